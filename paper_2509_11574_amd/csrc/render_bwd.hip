@@ -452,17 +452,13 @@ __global__ void __launch_bounds__(256) k_pose_reduce(const ViewTable* __restrict
     } else if (threadIdx.x == 0) {
         // the view was rendered from Exp(xi) T: the gradient with respect to xi is
         // J_l(xi)^T times the gradient of the left perturbation at that pose
-        double gz[6], xd[6], J[36];
+        double gz[6], xd[6], y[6];
         for (int q = 0; q < 6; ++q) {
             gz[q] = (double)(((red[0][q] + red[1][q]) + red[2][q]) + red[3][q]);
             xd[q] = (double)xi[q];
         }
-        se3_left_jacobian_d(xd, J);
-        for (int c = 0; c < 6; ++c) {
-            double a = 0.0;
-            for (int r = 0; r < 6; ++r) a += J[6 * r + c] * gz[r];
-            dpose[v * 6 + c] = (float)a;
-        }
+        se3_left_jacobian_t_mul_d(xd, gz, y);
+        for (int c = 0; c < 6; ++c) dpose[v * 6 + c] = (float)y[c];
     }
 }
 

