@@ -6,6 +6,7 @@
 //   k_remove_count    per block of 256 Gaussians: how many are kept
 //   k_remove_scan     one block: block offsets, kept total (the output row stride)
 //   k_remove_scatter  per Gaussian: its rows of every set to its kept position
+#include <algorithm>
 #include <cmath>
 
 #include "gps_internal.h"
@@ -145,8 +146,8 @@ gps_status launch_remove_gaussians(const gps_removal_cfg* cfg, const gps_gaussia
 //   k_insert_flags  per pixel: mask (bit 0) and sample (bit 1) flags and the
 //                   mask depth (the depth on mask pixels, 0 elsewhere); per
 //                   block of 256 pixels, the number taken
-//   k_insert_bits   per 8x8 pixel block: a 64-bit word of its mask pixels
-//   k_insert_scan   one block: block offsets, total taken -> out_count
+//   k_insert_scan_bits  block 0: block offsets, total taken -> out_count; the others:
+//                   per 8x8 pixel block, a 64-bit word of its mask pixels
 //   k_insert_place  per taken pixel: its row-major output position
 //   k_insert_init   per new Gaussian: its surface point, normal, scale (the
 //                   three nearest mask vertices over the whole mask), rotation
@@ -193,25 +194,26 @@ __global__ void __launch_bounds__(256) k_insert_flags(InsertArgs a)
     if (threadIdx.x == 0) a.blk_cnt[blockIdx.x] = tot;
 }
 
-// One wavefront per 8x8 pixel block: lane 8 r + c holds pixel (8 bx + c, 8 by + r).
-__global__ void __launch_bounds__(256) k_insert_bits(InsertArgs a)
-{
-    const int blk = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (blk >= a.nbx * a.nby) return;  // uniform per wavefront
-    const int bx = blk % a.nbx, by = blk / a.nbx;
-    const int px = bx * 8 + (lane & 7), py = by * 8 + (lane >> 3);
-    const bool m = px < a.cam.W && py < a.cam.H && a.mdepth[(size_t)py * a.cam.W + px] > 0.0f;
-    const unsigned long long word = __ballot(m);
-    if (lane == 0) a.bits[blk] = word;
-}
-
-__global__ void __launch_bounds__(1024) k_insert_scan(InsertArgs a, int nblk)
+// Two things that depend on the flags alone, in one launch: block 0 scans the counts of
+// the flag blocks; each wavefront of the others packs one 8x8 pixel block's mask (lane 8 r + c
+// holds pixel (8 bx + c, 8 by + r)).
+__global__ void __launch_bounds__(1024) k_insert_scan_bits(InsertArgs a, int nblk)
 {
     __shared__ unsigned int wsum[16];
     __shared__ unsigned int carry_s;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (blockIdx.x > 0) {
+        const int blk = ((int)blockIdx.x - 1) * 16 + wid;
+        if (blk >= a.nbx * a.nby) return;  // uniform per wavefront
+        const int bx = blk % a.nbx, by = blk / a.nbx;
+        const int px = bx * 8 + (lane & 7), py = by * 8 + (lane >> 3);
+        const bool m = px < a.cam.W && py < a.cam.H && a.mdepth[(size_t)py * a.cam.W + px] > 0.0f;
+        const unsigned long long word = __ballot(m);
+        if (lane == 0) a.bits[blk] = word;
+        return;
+    }
     if (threadIdx.x == 0) carry_s = 0u;
     __syncthreads();
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int base = 0; base < nblk; base += 1024) {
         const int i = base + threadIdx.x;
         const unsigned int c = i < nblk ? a.blk_cnt[i] : 0u;
@@ -266,15 +268,23 @@ __global__ void __launch_bounds__(256) k_insert_place(InsertArgs a)
     if (pos < (unsigned int)a.capacity) a.list[pos] = p;
 }
 
-// Per new Gaussian (position pos < min(sampled, capacity)).
-__global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
+// The three smallest of two ascending triples, ascending.
+__device__ __forceinline__ void merge3(float& a0, float& a1, float& a2, float c0, float c1, float c2)
+{
+    const float m1 = fminf(fminf(a1, c1), fmaxf(a0, c0));
+    const float m2 = fminf(fminf(a2, c2), fminf(fmaxf(a0, c1), fmaxf(a1, c0)));
+    a0 = fminf(a0, c0);
+    a1 = m1;
+    a2 = m2;
+}
+
+// New Gaussian `pos` (Appendix A) with first scale s1, by one lane.
+__device__ __forceinline__ void write_gaussian(const InsertArgs& a, unsigned int pos, float s1)
 {
     const int W = a.cam.W, H = a.cam.H, n = W * H;
-    const unsigned int pos = blockIdx.x * 256 + threadIdx.x;
-    if (pos >= *a.total || pos >= (unsigned int)a.capacity) return;
+    const DevCam& c = a.cam;
     const int p = a.list[pos];
     const int i = p % W, j = p / W;
-    const DevCam& c = a.cam;
     float X[3];
     cam_point(c, i, j, a.depth[p], X);
     // normal: central differences of the vertex map, facing the camera (at -X)
@@ -306,89 +316,6 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
         nv[k] = c.R[k] * nc[0] + c.R[3 + k] * nc[1] + c.R[6 + k] * nc[2];
         V[k] = c.R[k] * xt[0] + c.R[3 + k] * xt[1] + c.R[6 + k] * xt[2];
     }
-    // The three nearest other mask vertices over the whole mask (Appendix A), by
-    // rings of 8x8 blocks around the query's block.  A pixel column c beyond the
-    // scanned window holds only points of the half-space fx x - (c - cx) z <= 0
-    // (or >= 0), so no unscanned vertex is nearer than the distance from X to the
-    // nearest such plane: the search stops once the third distance is within it.
-    // A third distance above sqrt(3) scale_cap gives s1 = scale_cap whatever the
-    // exact neighbours are, so the rings stop there as well once three are held.
-    const float r2max = 3.0f * a.scale_cap * a.scale_cap;
-    float b0 = INFINITY, b1 = INFINITY, b2 = INFINITY;  // squared distances, ascending
-    int cnt = 0;
-    const int bi = i >> 3, bj = j >> 3;
-    // Distance from X (on the ray of pixel column i, depth Z) to the plane through the
-    // camera centre holding the rays of column c: |i - c| Z / |(fx, c - cx)| (the
-    // integer difference is exact, so the bound has no cancellation); rows alike.
-    auto plane_dist = [&](int q, int cq, float f, float cc) {
-        const float k = (float)cq - cc;
-        return (float)abs(q - cq) * X[2] / sqrtf(f * f + k * k);
-    };
-    // lower bound of the distance from X to any point of pixel columns [c0, c1], rows [r0, r1]
-    auto box_bound = [&](int c0, int c1, int r0, int r1) {
-        float lx = 0.0f, ly = 0.0f;
-        if (c0 > i) lx = plane_dist(i, c0, c.fx, c.cx);
-        else if (c1 < i) lx = plane_dist(i, c1, c.fx, c.cx);
-        if (r0 > j) ly = plane_dist(j, r0, c.fy, c.cy);
-        else if (r1 < j) ly = plane_dist(j, r1, c.fy, c.cy);
-        return fmaxf(lx, ly) * (1.0f - 1e-4f);  // rounding margin: never above the true bound
-    };
-    for (int r = 0;; ++r) {
-        const int bx0 = bi - r, bx1 = bi + r, by0 = bj - r, by1 = bj + r;
-        for (int by = max(by0, 0); by <= min(by1, a.nby - 1); ++by) {
-            const bool full = by == by0 || by == by1;  // top and bottom rows of the ring: every block
-            for (int bx = bx0; bx <= bx1; bx = full ? bx + 1 : (bx == bx0 ? bx1 : bx1 + 1)) {
-                if (bx < 0 || bx >= a.nbx) continue;
-                const int c0 = bx * 8, r0 = by * 8;
-                if (cnt >= 3) {
-                    const float lb = box_bound(c0, min(c0 + 7, W - 1), r0, min(r0 + 7, H - 1));
-                    if (lb * lb >= b2) continue;
-                }
-                unsigned long long word = a.bits[(size_t)by * a.nbx + bx];
-                while (word) {
-                    const int k = __ffsll((long long)word) - 1;
-                    word &= word - 1ull;
-                    const int ii = c0 + (k & 7), jj = r0 + (k >> 3);
-                    if (ii == i && jj == j) continue;
-                    float U[3];
-                    cam_point(c, ii, jj, a.mdepth[(size_t)jj * W + ii], U);
-                    const float d2 = (U[0] - X[0]) * (U[0] - X[0]) + (U[1] - X[1]) * (U[1] - X[1]) +
-                                     (U[2] - X[2]) * (U[2] - X[2]);
-                    ++cnt;
-                    if (d2 < b2) {
-                        if (d2 < b1) {
-                            b2 = b1;
-                            if (d2 < b0) {
-                                b1 = b0;
-                                b0 = d2;
-                            } else {
-                                b1 = d2;
-                            }
-                        } else {
-                            b2 = d2;
-                        }
-                    }
-                }
-            }
-        }
-        // distance bound of everything outside the scanned window
-        const int x0 = max(bx0, 0) * 8, x1 = min(bx1 * 8 + 7, W - 1);
-        const int y0 = max(by0, 0) * 8, y1 = min(by1 * 8 + 7, H - 1);
-        float bound = INFINITY;
-        if (x0 > 0) bound = fminf(bound, box_bound(0, x0 - 1, j, j));
-        if (x1 < W - 1) bound = fminf(bound, box_bound(x1 + 1, W - 1, j, j));
-        if (y0 > 0) bound = fminf(bound, box_bound(i, i, 0, y0 - 1));
-        if (y1 < H - 1) bound = fminf(bound, box_bound(i, i, y1 + 1, H - 1));
-        if (bound == INFINITY) break;                       // the whole image is scanned
-        if (cnt >= 3 && b2 <= bound * bound) break;         // exact: nothing unscanned is nearer
-        if (cnt >= 3 && bound * bound >= r2max) break;      // the third is beyond sqrt(3) cap: capped
-    }
-    float s1 = a.scale_cap;
-    if (cnt > 0) {
-        const int m = cnt < 3 ? cnt : 3;
-        const float sum = m == 1 ? b0 : (m == 2 ? b0 + b1 : (b0 + b1) + b2);
-        s1 = fminf(a.scale_cap, sqrtf(sum / (float)m));  // root mean square distance
-    }
     // shortest-arc rotation taking the local z axis onto the normal; for a normal
     // near -z the scalar part 1 + n_z is formed as (n_x^2 + n_y^2) / (1 - n_z), its
     // value on the unit sphere, so that the rounding of the normalisation cannot
@@ -418,6 +345,154 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
     for (int k = 0; k < 3; ++k) a.out[4][k * C + pos] = a.frame_rgb[k * HW + p];
     for (int r = 0; r < a.sh_rows; ++r) a.out[5][r * C + pos] = 0.0f;
     if (a.out_pixel) a.out_pixel[pos] = p;
+}
+
+// Per new Gaussian (position pos < min(sampled, capacity)): kNN lanes search its nearest
+// mask vertices together, then one lane of the block per Gaussian writes it.
+//
+// The search is a chain of dependent loads (a block's word, then the depths of its mask
+// pixels), so it is bound by latency: with one lane per Gaussian (72 blocks for the 18.4 k
+// Gaussians of a 1280x720 keyframe) it took 170 us, most of the chip idle.  Sixteen
+// lanes (a quarter of a wavefront, so that the group's exchanges stay in DPP rows) split each 8x8
+// block's 64 pixels four to a lane, read the words of up to 16 blocks of a ring in one round
+// trip, and keep a triple of smallest distances per lane that is merged once per ring; the
+// three smallest values are the same whatever the order of the search.
+// The grid is bounded (the number of new Gaussians is only known on the device, and a capacity
+// of every pixel would launch 57,600 blocks at 1280x720, most of them empty); blocks stride.
+constexpr int kNN = 16;
+constexpr unsigned int kInitGrid = 2048;
+
+__global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
+{
+    const int W = a.cam.W, H = a.cam.H;
+    constexpr int kPer = 256 / kNN;  // Gaussians per block
+    __shared__ float s_scale[kPer];
+    const unsigned int count = min(*a.total, (unsigned int)a.capacity);
+    const DevCam& c = a.cam;
+    for (unsigned int pos0 = blockIdx.x * kPer; pos0 < count; pos0 += gridDim.x * kPer) {  // the same for the whole block
+        const unsigned int qpos = pos0 + threadIdx.x / kNN;
+        if (qpos < count) {
+            const int l = threadIdx.x % kNN;
+            const int p = a.list[qpos];
+            const int i = p % W, j = p / W;
+            float X[3];
+            cam_point(c, i, j, a.depth[p], X);
+            // The three nearest other mask vertices over the whole mask (Appendix A), by
+            // rings of 8x8 blocks around the query's block.  A pixel column c beyond the
+            // scanned window holds only points of the half-space fx x - (c - cx) z <= 0
+            // (or >= 0), so no unscanned vertex is nearer than the distance from X to the
+            // nearest such plane: the search stops once the third distance is within it.
+            // A third distance above sqrt(3) scale_cap gives s1 = scale_cap whatever the
+            // exact neighbours are, so the rings stop there as well once three are held.
+            const float r2max = 3.0f * a.scale_cap * a.scale_cap;
+            float l0 = INFINITY, l1 = INFINITY, l2 = INFINITY;  // this lane's squared distances, ascending
+            float b0 = INFINITY, b1 = INFINITY, b2 = INFINITY;  // the group's
+            int cnt = 0;                                        // vertices scanned by the group
+            const int bi = i >> 3, bj = j >> 3;
+            // Distance from X (on the ray of pixel column i, depth Z) to the plane through the
+            // camera centre holding the rays of column c: |i - c| Z / |(fx, c - cx)| (the
+            // integer difference is exact, so the bound has no cancellation); rows alike.
+            auto plane_dist = [&](int q, int cq, float f, float cc) {
+                const float k = (float)cq - cc;
+                return (float)abs(q - cq) * X[2] / sqrtf(f * f + k * k);
+            };
+            // lower bound of the distance from X to any point of pixel columns [c0, c1], rows [r0, r1]
+            auto box_bound = [&](int c0, int c1, int r0, int r1) {
+                float lx = 0.0f, ly = 0.0f;
+                if (c0 > i) lx = plane_dist(i, c0, c.fx, c.cx);
+                else if (c1 < i) lx = plane_dist(i, c1, c.fx, c.cx);
+                if (r0 > j) ly = plane_dist(j, r0, c.fy, c.cy);
+                else if (r1 < j) ly = plane_dist(j, r1, c.fy, c.cy);
+                return fmaxf(lx, ly) * (1.0f - 1e-4f);  // rounding margin: never above the true bound
+            };
+            for (int r = 0;; ++r) {
+                const int bx0 = bi - r, bx1 = bi + r, by0 = bj - r, by1 = bj + r;
+                // The ring's blocks in the order top row, bottom row, left and right columns.
+                const int ring = r == 0 ? 1 : 8 * r, side = 2 * r + 1;
+                for (int q0 = 0; q0 < ring; q0 += kNN) {
+                    // lane l looks at block q0 + l: in the image, and near enough to matter
+                    const int q = q0 + l;
+                    int bx, by;
+                    if (q < side) bx = bx0 + q, by = by0;
+                    else if (q < 2 * side) bx = bx0 + q - side, by = by1;
+                    else bx = (q & 1) ? bx1 : bx0, by = by0 + 1 + ((q - 2 * side) >> 1);
+                    bool want = q < ring && bx >= 0 && bx < a.nbx && by >= 0 && by < a.nby;
+                    if (want && cnt >= 3) {
+                        const float lb = box_bound(bx * 8, min(bx * 8 + 7, W - 1), by * 8, min(by * 8 + 7, H - 1));
+                        want = !(lb * lb >= b2);
+                    }
+                    const unsigned long long mine = want ? a.bits[(size_t)by * a.nbx + bx] : 0ull;
+                    // blocks of this batch that hold mask pixels, as bits of the group's lanes
+                    unsigned int have = (unsigned int)(__ballot(mine != 0ull) >> (threadIdx.x & 48)) & 0xffffu;
+                    const int at = bx | (by << 16);
+                    while (have) {
+                        const int src = __ffs((int)have) - 1;
+                        have &= have - 1u;
+                        const unsigned int lo = __shfl((unsigned int)mine, src, kNN);
+                        const unsigned int hi = __shfl((unsigned int)(mine >> 32), src, kNN);
+                        const int xy = __shfl(at, src, kNN);
+                        cnt += __popc(lo) + __popc(hi);
+                        // this lane's four pixels of the block: row l / 2, columns 4 (l & 1) .. + 3
+                        unsigned int nib = ((l < 8 ? lo : hi) >> (4 * (l & 7))) & 0xfu;
+                        const int jj = (xy >> 16) * 8 + (l >> 1), ii0 = (xy & 0xffff) * 8 + 4 * (l & 1);
+                        while (nib) {
+                            const int ii = ii0 + __ffs((int)nib) - 1;
+                            nib &= nib - 1u;
+                            if (ii == i && jj == j) continue;
+                            float U[3];
+                            cam_point(c, ii, jj, a.mdepth[(size_t)jj * W + ii], U);
+                            const float d2 = (U[0] - X[0]) * (U[0] - X[0]) + (U[1] - X[1]) * (U[1] - X[1]) +
+                                             (U[2] - X[2]) * (U[2] - X[2]);
+                            if (d2 < l2) {
+                                if (d2 < l1) {
+                                    l2 = l1;
+                                    if (d2 < l0) {
+                                        l1 = l0;
+                                        l0 = d2;
+                                    } else {
+                                        l1 = d2;
+                                    }
+                                } else {
+                                    l2 = d2;
+                                }
+                            }
+                        }
+                    }
+                }
+                if (r == 0) --cnt;  // the query is a mask pixel of its own block
+                b0 = l0, b1 = l1, b2 = l2;
+#pragma unroll
+                for (int m = 1; m < kNN; m <<= 1) {
+                    const float c0 = __shfl_xor(b0, m, kNN), c1 = __shfl_xor(b1, m, kNN), c2 = __shfl_xor(b2, m, kNN);
+                    merge3(b0, b1, b2, c0, c1, c2);
+                }
+                // distance bound of everything outside the scanned window
+                const int x0 = max(bx0, 0) * 8, x1 = min(bx1 * 8 + 7, W - 1);
+                const int y0 = max(by0, 0) * 8, y1 = min(by1 * 8 + 7, H - 1);
+                float bound = INFINITY;
+                if (x0 > 0) bound = fminf(bound, box_bound(0, x0 - 1, j, j));
+                if (x1 < W - 1) bound = fminf(bound, box_bound(x1 + 1, W - 1, j, j));
+                if (y0 > 0) bound = fminf(bound, box_bound(i, i, 0, y0 - 1));
+                if (y1 < H - 1) bound = fminf(bound, box_bound(i, i, y1 + 1, H - 1));
+                if (bound == INFINITY) break;                       // the whole image is scanned
+                if (cnt >= 3 && b2 <= bound * bound) break;         // exact: nothing unscanned is nearer
+                if (cnt >= 3 && bound * bound >= r2max) break;      // the third is beyond sqrt(3) cap: capped
+            }
+            if (l == 0) {
+                float s1 = a.scale_cap;
+                if (cnt > 0) {
+                    const int m = cnt < 3 ? cnt : 3;
+                    const float sum = m == 1 ? b0 : (m == 2 ? b0 + b1 : (b0 + b1) + b2);
+                    s1 = fminf(a.scale_cap, sqrtf(sum / (float)m));  // root mean square distance
+                }
+                s_scale[threadIdx.x / kNN] = s1;
+            }
+        }
+        __syncthreads();
+        const unsigned int pos = pos0 + threadIdx.x;
+        if (threadIdx.x < kPer && pos < count) write_gaussian(a, pos, s_scale[threadIdx.x]);
+        __syncthreads();
+    }
 }
 
 size_t insertion_workspace_bytes(int W, int H)
@@ -468,12 +543,11 @@ gps_status launch_insert_gaussians(const gps_insert_cfg* cfg, const DevCam& cam,
     a.bits = reinterpret_cast<unsigned long long*>(ws + 3 * al(4 * n) + 2 * al(4 * nb) + 256);
     const int nbits = a.nbx * a.nby;
     if (nblk > 0) GPS_LAUNCH(K_INSERT, s, k_insert_flags, dim3(nblk), dim3(256), 0, s, a);
-    if (nbits > 0) GPS_LAUNCH(K_INSERT, s, k_insert_bits, dim3((nbits + 3) / 4), dim3(256), 0, s, a);
-    GPS_LAUNCH(K_INSERT, s, k_insert_scan, dim3(1), dim3(1024), 0, s, a, nblk);
+    GPS_LAUNCH(K_INSERT, s, k_insert_scan_bits, dim3(1 + (nbits + 15) / 16), dim3(1024), 0, s, a, nblk);
     const size_t cap = (size_t)a.capacity < n ? (size_t)a.capacity : n;
     if (nblk > 0 && cap > 0) {
         GPS_LAUNCH(K_INSERT, s, k_insert_place, dim3(nblk), dim3(256), 0, s, a);
-        GPS_LAUNCH(K_INSERT, s, k_insert_init, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, a);
+        GPS_LAUNCH(K_INSERT, s, k_insert_init, dim3(std::min((unsigned)((cap + 256 / kNN - 1) / (256 / kNN)), kInitGrid)), dim3(256), 0, s, a);
     }
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
