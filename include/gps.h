@@ -313,8 +313,11 @@ gps_status gps_hash_fuse(const gps_hash_volume* vol, const gps_camera* cam, cons
  * view is formed first, and the rays of a tile march only over their samples in
  * that interval (every sample outside it has a stencil of unallocated points, so
  * it reads positive and the crossing is the same); the free space in front of the
- * first block costs nothing.  NULL: the rays march the whole region.  Two kernels,
- * four with range.  GPS_ERR_INVALID_ARG for a range shorter than needed. */
+ * first block costs nothing.  NULL: the rays march the whole region.  Regions of up
+ * to 32768 blocks (and 1536 32-block words of rows) with a capacity of up to 65535
+ * are marched with a block directory in LDS, which passes free space by itself: range
+ * is checked but not written.  Two kernels, four where range is used.
+ * GPS_ERR_INVALID_ARG for a range shorter than needed. */
 #define GPS_HASH_TILE 16
 #define GPS_HASH_RANGE_FLOATS(width, height) \
     (2 * (((width) + GPS_HASH_TILE - 1) / GPS_HASH_TILE) * (((height) + GPS_HASH_TILE - 1) / GPS_HASH_TILE))

@@ -18,8 +18,10 @@
 //   k_hash_fuse      one 512-lane group per visible block (groups stride over the
 //                    list): the dense fusion update of every point
 //   k_hash_block_min the minimum tsdf of each allocated block
-//   k_hash_raycast   the dense march over the region's box; a sample whose stencil
-//                    lies in one block that is unallocated or all positive reads
+//   k_hash_raycast_dir  the dense march over the region's box with the block directory of
+//                    the whole region in LDS (regions of up to kDirBlocks blocks)
+//   k_hash_raycast   the march with table lookups (larger regions); in both a sample whose
+//                    stencil lies in blocks that are unallocated or all positive reads
 //                    positive, so such samples are skipped
 // The pool order depends on which lane inserts a key first; no value depends on it.
 #include <cmath>
@@ -475,6 +477,173 @@ __global__ void __launch_bounds__(256) k_hash_range(HashDev h, MarchArgs a, Hash
     }
 }
 
+// The raycast with the region's block directory in LDS.  With table lookups a step of the march
+// is a chain of dependent global loads (key, slot, minimum, values) and the rays of a wavefront wait
+// for the longest: 452 us for a 1280x720 view of a 256^3 region (2.7 k blocks allocated), and
+// 28 us for the depth ranges that keep the rays out of the free space.  Here each
+// workgroup first writes, from the list of allocated blocks,
+//   dir   one 16-bit pool block per block of the region (0xffff: unallocated), and
+//   bit planes over the region's blocks, rows of x padded to words: `own` (the block's
+//         points are all positive), `all` (its own and its seven +x, +y, +z neighbours': every
+//         stencil based in it is positive), `sup` (all of a 4^3 group of blocks),
+// about 3 us, and then its wavefronts march 8x8-pixel tiles, all lookups in LDS, free space in
+// steps of up to 32 voxels, so no depth ranges are formed.  The same samples decide the crossing.
+// A region of kDirBlocks blocks takes 72 KB, so that two workgroups of 16 wavefronts fill a
+// compute unit; that, and pool blocks below 0xffff, is where the line to the table lookups lies.
+constexpr int kDirBlocks = 32768;
+constexpr int kDirWords = 1536;  // words of one bit plane
+constexpr unsigned int kDirNone = 0xffffu;
+constexpr int kDirThreads = 1024;
+
+struct HashDirField {
+    const float* tsdf;
+    const float* rgb;
+    size_t pool;
+    const unsigned short* dir;
+    const unsigned int* own;
+    const unsigned int* all;
+    const unsigned int* sup;
+    int nb0, nb1, wx, sn1;  // blocks per axis, words per row, 4-block rows per axis
+
+    __device__ __forceinline__ bool depth_range(int, int, int, float*, float*) const { return false; }
+
+    __device__ __forceinline__ void fetch8(int plane, const int b[3], float q[8]) const
+    {
+        const float* f = plane == 0 ? tsdf : rgb + (size_t)(plane - 1) * pool;
+        const float dflt = plane == 0 ? 1.0f : 0.0f;
+        const int X = b[0] >> 3, l0 = b[0] & 7;
+        const bool cx = l0 == 7;  // the stencil's right half lies in the next block
+        const unsigned int lx = (unsigned int)min(l0, 6);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int y = b[1] + (k & 1), z = b[2] + (k >> 1);
+            const int lin = X + nb0 * ((y >> 3) + nb1 * (z >> 3));
+            const unsigned int e = dir[lin];
+            const unsigned int row = (unsigned int)((y & 7) * kHB + (z & 7) * kHB * kHB);
+            // an unallocated block reads pool block 0 and drops the values; both halves of the row
+            // come in one load, which stays inside the row
+            const float* p = f + ((e == kDirNone ? 0u : e) * (unsigned int)kHB3 + row + lx);
+            const float v0 = p[0], v1 = p[1];
+            q[2 * k] = e == kDirNone ? dflt : (cx ? v1 : v0);
+            q[2 * k + 1] = e == kDirNone ? dflt : v1;
+        }
+        if (cx) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int y = b[1] + (k & 1), z = b[2] + (k >> 1);
+                const unsigned int e = dir[X + 1 + nb0 * ((y >> 3) + nb1 * (z >> 3))];
+                const unsigned int row = (unsigned int)((y & 7) * kHB + (z & 7) * kHB * kHB);
+                const float v = f[(e == kDirNone ? 0u : e) * (unsigned int)kHB3 + row];
+                q[2 * k + 1] = e == kDirNone ? dflt : v;
+            }
+        }
+    }
+
+    __device__ __forceinline__ bool skip_box(const int b[3], float lo[3], float hi[3]) const
+    {
+        const int X = b[0] >> 3, Y = b[1] >> 3, Z = b[2] >> 3;
+        const unsigned int bit = 1u << (X & 31);
+        const int w = wx * (Y + nb1 * Z) + (X >> 5);
+        const unsigned int ws = sup[wx * ((Y >> 2) + sn1 * (Z >> 2)) + (X >> 5)], wa = all[w], wo = own[w];
+        if (ws & bit) {
+            lo[0] = (float)((X & ~3) * kHB), lo[1] = (float)((Y & ~3) * kHB), lo[2] = (float)((Z & ~3) * kHB);
+            hi[0] = lo[0] + (float)(4 * kHB), hi[1] = lo[1] + (float)(4 * kHB), hi[2] = lo[2] + (float)(4 * kHB);
+            return true;
+        }
+        // samples based at local positions 0..6 have their whole stencil in the block
+        const bool inner = (b[0] & 7) < 7 && (b[1] & 7) < 7 && (b[2] & 7) < 7;
+        if (!(wa & bit) && !((wo & bit) && inner)) return false;
+        const float edge = (wa & bit) ? (float)kHB : (float)(kHB - 1);
+        lo[0] = (float)(X * kHB), lo[1] = (float)(Y * kHB), lo[2] = (float)(Z * kHB);
+        hi[0] = lo[0] + edge, hi[1] = lo[1] + edge, hi[2] = lo[2] + edge;
+        return true;
+    }
+};
+
+// LDS words of the directory and the bit planes, in this order: dir, own, all, sup.
+struct HashDirShape {
+    int nb[3], wx, sn1, sn2;
+    int dir_words, plane_words, sup_words;
+};
+
+__global__ void __launch_bounds__(kDirThreads, 8) k_hash_raycast_dir(MarchArgs a, HashDev h, HashDirShape sh, int n_tiles)
+{
+    extern __shared__ unsigned int lds[];
+    unsigned int* dirw = lds;
+    unsigned int* own = lds + sh.dir_words;
+    unsigned int* all = own + sh.plane_words;
+    unsigned int* sup = all + sh.plane_words;
+    for (int i = threadIdx.x; i < sh.dir_words + sh.plane_words; i += kDirThreads) lds[i] = 0xffffffffu;
+    __syncthreads();
+    const int n = min(h.state[0], h.cap);
+    for (int i = threadIdx.x; i < n; i += kDirThreads) {
+        int b[3];
+        hash_unkey(h.bkey[i], b);
+        if (b[0] >= sh.nb[0] || b[1] >= sh.nb[1] || b[2] >= sh.nb[2]) continue;
+        const int lin = b[0] + sh.nb[0] * (b[1] + sh.nb[1] * b[2]);
+        // 32-bit atomics: entries that share a word never meet in a partial store
+        const int half = (lin & 1) * 16;
+        atomicAnd(dirw + (lin >> 1), ~(0xffffu << half) | ((unsigned int)i << half));
+        if (!(h.bmin && h.bmin[i] > kBrickPositive))
+            atomicAnd(own + sh.wx * (b[1] + sh.nb[1] * b[2]) + (b[0] >> 5), ~(1u << (b[0] & 31)));
+    }
+    __syncthreads();
+    // blocks past the region's edge hold no stencil and count as positive
+    for (int i = threadIdx.x; i < sh.plane_words; i += kDirThreads) {
+        const int xw = i % sh.wx, y = (i / sh.wx) % sh.nb[1], z = i / (sh.wx * sh.nb[1]);
+        unsigned int acc = 0xffffffffu;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int yy = y + (k & 1), zz = z + (k >> 1);
+            if (yy >= sh.nb[1] || zz >= sh.nb[2]) continue;
+            const int r = sh.wx * (yy + sh.nb[1] * zz) + xw;
+            const unsigned int w0 = own[r], w1 = xw + 1 < sh.wx ? own[r + 1] : 0xffffffffu;
+            acc &= w0 & ((w0 >> 1) | (w1 << 31));
+        }
+        all[i] = acc;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < sh.sup_words; i += kDirThreads) {
+        const int xw = i % sh.wx, y4 = (i / sh.wx) % sh.sn1, z4 = i / (sh.wx * sh.sn1);
+        unsigned int acc = 0xffffffffu;
+        for (int k = 0; k < 16; ++k) {
+            const int yy = 4 * y4 + (k & 3), zz = 4 * z4 + (k >> 2);
+            if (yy < sh.nb[1] && zz < sh.nb[2]) acc &= all[sh.wx * (yy + sh.nb[1] * zz) + xw];
+        }
+        acc &= acc >> 1;
+        acc &= acc >> 2;
+        sup[i] = (acc & 0x11111111u) * 0xfu;  // every block of a group carries the group's bit
+    }
+    __syncthreads();
+    HashDirField f;
+    f.tsdf = h.tsdf;
+    f.rgb = h.rgb;
+    f.pool = h.pool;
+    f.dir = reinterpret_cast<const unsigned short*>(dirw);
+    f.own = own;
+    f.all = all;
+    f.sup = sup;
+    f.nb0 = sh.nb[0];
+    f.nb1 = sh.nb[1];
+    f.wx = sh.wx;
+    f.sn1 = sh.sn1;
+    // Tiles of 8x8 pixels, numbered over the views; neighbouring tiles go to different workgroups.
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int t = wid * (int)gridDim.x + (int)blockIdx.x; t < n_tiles; t += (int)gridDim.x * (kDirThreads / 64)) {
+        int view = 0, lt = t;
+        for (; view + 1 < a.n_views; ++view) {
+            const int nt = ((a.cams[view].W + 7) >> 3) * ((a.cams[view].H + 7) >> 3);
+            if (lt < nt) break;
+            lt -= nt;
+        }
+        const DevCam& c = a.cams[view];
+        const int tx = (c.W + 7) >> 3;
+        const int col = (lt % tx) * 8 + (lane & 7), row = (lt / tx) * 8 + (lane >> 3);
+        if (col < c.W && row < c.H) march_pixel(a, f, view, col, row);
+    }
+}
+
 __global__ void __launch_bounds__(256) k_hash_raycast(MarchArgs a, HashDev h, HashRange hr)
 {
     const int view = blockIdx.z;
@@ -555,6 +724,22 @@ gps_status launch_hash_fuse(const gps_hash_volume* v, const gps_camera* cam, con
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 
+// The directory's shape, and whether the region and the pool fit it.
+static bool hash_dir_shape(const HashDev& h, HashDirShape* sh)
+{
+    const long long blocks = (long long)h.nb[0] * h.nb[1] * h.nb[2];
+    const long long wx = (h.nb[0] + 31) / 32, words = wx * h.nb[1] * h.nb[2];
+    if (blocks > kDirBlocks || words > kDirWords || h.cap > (int)kDirNone) return false;
+    for (int k = 0; k < 3; ++k) sh->nb[k] = h.nb[k];
+    sh->wx = (int)wx;
+    sh->sn1 = (h.nb[1] + 3) / 4;
+    sh->sn2 = (h.nb[2] + 3) / 4;
+    sh->dir_words = (int)((blocks + 1) / 2);
+    sh->plane_words = (int)words;
+    sh->sup_words = sh->wx * sh->sn1 * sh->sn2;
+    return true;
+}
+
 size_t hash_range_floats(const gps_camera* cams, int n_views)
 {
     size_t n = 0;
@@ -573,6 +758,17 @@ gps_status launch_hash_raycast(const gps_hash_volume* v, const gps_camera* cams,
     const HashDev h = hash_dev(*v);
     const int bgrid = v->capacity < kHashGrid ? v->capacity : kHashGrid;
     if (v->block_min) GPS_LAUNCH(K_BRICK_MIN, s, k_hash_block_min, dim3((bgrid + 3) / 4), dim3(256), 0, s, h);
+    HashDirShape sh;
+    if (hash_dir_shape(h, &sh)) {
+        long long tiles = 0;
+        for (int k = 0; k < n_views; ++k) tiles += (long long)((cams[k].width + 7) / 8) * ((cams[k].height + 7) / 8);
+        if (tiles < (1ll << 31) - (1 << 20)) {
+            const size_t bytes = 4 * (size_t)(sh.dir_words + 2 * sh.plane_words + sh.sup_words);
+            const int groups = tiles < 512 ? (int)tiles : 512;  // two a compute unit
+            GPS_LAUNCH(K_RAYCAST, s, k_hash_raycast_dir, dim3(groups), dim3(kDirThreads), bytes, s, a, h, sh, (int)tiles);
+            return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
+        }
+    }
     HashRange hr;
     hr.range = nullptr;
     if (range) {
