@@ -368,16 +368,14 @@ struct HashField {
 
     // Samples based at local positions 0..6 of a block have their whole stencil in it:
     // positive when the block is unallocated or its minimum is positive.
-    __device__ __forceinline__ bool skip_box(const int b[3], float lo[3], float hi[3]) const
+    __device__ __forceinline__ bool skip_box(const int b[3], float lo[3], float* edge) const
     {
         if ((b[0] & 7) == 7 || (b[1] & 7) == 7 || (b[2] & 7) == 7) return false;
         const int blk = block_of(b[0] >> 3, b[1] >> 3, b[2] >> 3);
         if (blk >= 0 && !(h.bmin && h.bmin[blk] > kBrickPositive)) return false;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            lo[k] = (float)((b[k] >> 3) * kHB);
-            hi[k] = lo[k] + (float)(kHB - 1);
-        }
+        for (int k = 0; k < 3; ++k) lo[k] = (float)((b[k] >> 3) * kHB);
+        *edge = (float)(kHB - 1);
         return true;
     }
 };
@@ -488,6 +486,7 @@ __global__ void __launch_bounds__(256) k_hash_range(HashDev h, MarchArgs a, Hash
 //         stencil based in it is positive), `sup` (all of a 4^3 group of blocks),
 // about 3 us, and then its wavefronts march 8x8-pixel tiles, all lookups in LDS, free space in
 // steps of up to 32 voxels, so no depth ranges are formed.  The same samples decide the crossing.
+// 226 us for that view; what remains is the directory's arithmetic in front of each stencil.
 // A region of kDirBlocks blocks takes 72 KB, so that two workgroups of 16 wavefronts fill a
 // compute unit; that, and pool blocks below 0xffff, is where the line to the table lookups lies.
 constexpr int kDirBlocks = 32768;
@@ -511,51 +510,63 @@ struct HashDirField {
     {
         const float* f = plane == 0 ? tsdf : rgb + (size_t)(plane - 1) * pool;
         const float dflt = plane == 0 ? 1.0f : 0.0f;
-        const int X = b[0] >> 3, l0 = b[0] & 7;
-        const bool cx = l0 == 7;  // the stencil's right half lies in the next block
+        const int l0 = b[0] & 7, l1 = b[1] & 7, l2 = b[2] & 7;
+        const bool cx = l0 == 7, cy = l1 == 7, cz = l2 == 7;  // the axes along which the stencil crosses
+        const int lin = (b[0] >> 3) + nb0 * ((b[1] >> 3) + nb1 * (b[2] >> 3));
+        // the lanes of a wavefront march side by side (8x8 pixels are about a voxel), so the
+        // branches below are mostly taken or left by all of them
+        unsigned int e[4];
+        e[0] = dir[lin];
+        e[1] = e[2] = e[3] = e[0];
+        const int sy = cy ? nb0 : 0, sz = cz ? nb0 * nb1 : 0;
+        if (cy || cz) {
+            e[1] = dir[lin + sy];
+            e[2] = dir[lin + sz];
+            e[3] = dir[lin + sy + sz];
+        }
+        const unsigned int y0 = (unsigned int)(l1 * kHB), y1 = (unsigned int)(((l1 + 1) & 7) * kHB);
+        const unsigned int z0 = (unsigned int)(l2 * kHB * kHB), z1 = (unsigned int)(((l2 + 1) & 7) * kHB * kHB);
+        const unsigned int row[4] = {y0 + z0, y1 + z0, y0 + z1, y1 + z1};
         const unsigned int lx = (unsigned int)min(l0, 6);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int y = b[1] + (k & 1), z = b[2] + (k >> 1);
-            const int lin = X + nb0 * ((y >> 3) + nb1 * (z >> 3));
-            const unsigned int e = dir[lin];
-            const unsigned int row = (unsigned int)((y & 7) * kHB + (z & 7) * kHB * kHB);
             // an unallocated block reads pool block 0 and drops the values; both halves of the row
             // come in one load, which stays inside the row
-            const float* p = f + ((e == kDirNone ? 0u : e) * (unsigned int)kHB3 + row + lx);
+            const float* p = f + ((e[k] == kDirNone ? 0u : e[k]) * (unsigned int)kHB3 + row[k] + lx);
             const float v0 = p[0], v1 = p[1];
-            q[2 * k] = e == kDirNone ? dflt : (cx ? v1 : v0);
-            q[2 * k + 1] = e == kDirNone ? dflt : v1;
+            q[2 * k] = e[k] == kDirNone ? dflt : (cx ? v1 : v0);
+            q[2 * k + 1] = e[k] == kDirNone ? dflt : v1;
         }
         if (cx) {
+            e[0] = dir[lin + 1];
+            e[1] = e[2] = e[3] = e[0];
+            if (cy || cz) {
+                e[1] = dir[lin + 1 + sy];
+                e[2] = dir[lin + 1 + sz];
+                e[3] = dir[lin + 1 + sy + sz];
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int y = b[1] + (k & 1), z = b[2] + (k >> 1);
-                const unsigned int e = dir[X + 1 + nb0 * ((y >> 3) + nb1 * (z >> 3))];
-                const unsigned int row = (unsigned int)((y & 7) * kHB + (z & 7) * kHB * kHB);
-                const float v = f[(e == kDirNone ? 0u : e) * (unsigned int)kHB3 + row];
-                q[2 * k + 1] = e == kDirNone ? dflt : v;
+                const float v = f[(e[k] == kDirNone ? 0u : e[k]) * (unsigned int)kHB3 + row[k]];
+                q[2 * k + 1] = e[k] == kDirNone ? dflt : v;
             }
         }
     }
 
-    __device__ __forceinline__ bool skip_box(const int b[3], float lo[3], float hi[3]) const
+    __device__ __forceinline__ bool skip_box(const int b[3], float lo[3], float* edge) const
     {
         const int X = b[0] >> 3, Y = b[1] >> 3, Z = b[2] >> 3;
         const unsigned int bit = 1u << (X & 31);
         const int w = wx * (Y + nb1 * Z) + (X >> 5);
         const unsigned int ws = sup[wx * ((Y >> 2) + sn1 * (Z >> 2)) + (X >> 5)], wa = all[w], wo = own[w];
-        if (ws & bit) {
-            lo[0] = (float)((X & ~3) * kHB), lo[1] = (float)((Y & ~3) * kHB), lo[2] = (float)((Z & ~3) * kHB);
-            hi[0] = lo[0] + (float)(4 * kHB), hi[1] = lo[1] + (float)(4 * kHB), hi[2] = lo[2] + (float)(4 * kHB);
-            return true;
-        }
         // samples based at local positions 0..6 have their whole stencil in the block
         const bool inner = (b[0] & 7) < 7 && (b[1] & 7) < 7 && (b[2] & 7) < 7;
-        if (!(wa & bit) && !((wo & bit) && inner)) return false;
-        const float edge = (wa & bit) ? (float)kHB : (float)(kHB - 1);
-        lo[0] = (float)(X * kHB), lo[1] = (float)(Y * kHB), lo[2] = (float)(Z * kHB);
-        hi[0] = lo[0] + edge, hi[1] = lo[1] + edge, hi[2] = lo[2] + edge;
+        if (!((wa | (inner ? wo : 0u)) & bit)) return false;
+        const bool four = (ws & bit) != 0u;
+        const int mask = four ? -4 * kHB : -kHB;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lo[k] = (float)(b[k] & mask);
+        *edge = four ? (float)(4 * kHB) : ((wa & bit) ? (float)kHB : (float)(kHB - 1));
         return true;
     }
 };
@@ -569,6 +580,8 @@ struct HashDirShape {
 __global__ void __launch_bounds__(kDirThreads, 8) k_hash_raycast_dir(MarchArgs a, HashDev h, HashDirShape sh, int n_tiles)
 {
     extern __shared__ unsigned int lds[];
+    __shared__ unsigned int s_next;  // the workgroup's next tile
+    if (threadIdx.x == 0) s_next = 0u;
     unsigned int* dirw = lds;
     unsigned int* own = lds + sh.dir_words;
     unsigned int* all = own + sh.plane_words;
@@ -627,11 +640,16 @@ __global__ void __launch_bounds__(kDirThreads, 8) k_hash_raycast_dir(MarchArgs a
     f.nb1 = sh.nb[1];
     f.wx = sh.wx;
     f.sn1 = sh.sn1;
-    // Tiles of 8x8 pixels, numbered over the views; neighbouring tiles go to different workgroups.
+    // Tiles of 8x8 pixels, numbered over the views; neighbouring tiles go to different workgroups,
+    // and a workgroup's tiles to its wavefronts as they come free.  (Every lane takes
+    // part in the counter's increment, all but the first with 0: no branch around it.)
     const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int t = wid * (int)gridDim.x + (int)blockIdx.x; t < n_tiles; t += (int)gridDim.x * (kDirThreads / 64)) {
-        int view = 0, lt = t;
+    for (;;) {
+        const unsigned int ticket = (unsigned int)__builtin_amdgcn_readfirstlane(
+            (int)__hip_atomic_fetch_add(&s_next, lane == 0 ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        const long long t = (long long)ticket * gridDim.x + blockIdx.x;
+        if (t >= n_tiles) break;
+        int view = 0, lt = (int)t;
         for (; view + 1 < a.n_views; ++view) {
             const int nt = ((a.cams[view].W + 7) >> 3) * ((a.cams[view].H + 7) >> 3);
             if (lt < nt) break;

@@ -93,37 +93,44 @@ struct MarchArgs {
 //   void fetch8(int plane, const int b[3], float q[8]) const
 //       the values of plane 0 (tsdf) or 1..3 (colour) at the 2x2x2 stencil based
 //       at lattice point b (q[dx + 2 dy + 4 dz]; b and b + 1 inside the lattice);
-//   bool skip_box(const int b[3], float lo[3], float hi[3]) const
-//       true when every sample whose stencil base lies in the box [lo, hi) (lattice
+//   bool skip_box(const int b[3], float lo[3], float* edge) const
+//       true when every sample whose stencil base lies in the box [lo, lo + edge)^3 (lattice
 //       coordinates, containing b) reads positive; the box is then skipped;
 //   bool depth_range(int view, int col, int row, float* zlo, float* zhi) const
 //       true when every sample of the pixel's ray outside the camera depths
 //       [zlo, zhi] reads positive (zlo > zhi: all of them); false: no such bound.
 
-// binary32 trilinear of the tsdf (decision arithmetic); +1 where the stencil
-// leaves the lattice.
-template <class Fld>
-__device__ __forceinline__ float dec_trilinear(const MarchArgs& a, const Fld& fld, const float g[3], int* inside)
+// Sample at ray parameter lam: its lattice coordinates g (binary32, one rounding per
+// operation) and the base b of its stencil; whether the stencil lies in the lattice.
+__device__ __forceinline__ bool locate(const MarchArgs& a, const float o[3], const float dh[3], float lam, float g[3],
+                                       float fb[3], int b[3])
 {
 #pragma clang fp contract(off)
-    float b[3], fr[3];
-    int bi[3];
+    bool in = true;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        b[k] = floorf(g[k]);
-        fr[k] = g[k] - b[k];
+        float q = lam * dh[k];
+        q = o[k] + q;
+        q = q - a.origin[k];
+        g[k] = q * a.inv_voxel;
+        fb[k] = floorf(g[k]);
+        b[k] = (int)fb[k];
+        // (a float out of int's range saturates, so it is out of the lattice as well)
+        in = in && (unsigned int)b[k] <= (unsigned int)(a.n[k] - 2);
     }
+    return in;
+}
+
+// binary32 trilinear of the tsdf at a located sample (decision arithmetic).
+template <class Fld>
+__device__ __forceinline__ float dec_trilinear(const Fld& fld, const float g[3], const float fb[3], const int b[3])
+{
+#pragma clang fp contract(off)
+    float fr[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if (!(b[k] >= 0.0f && b[k] <= (float)(a.n[k] - 2))) {
-            *inside = 0;
-            return 1.0f;
-        }
-        bi[k] = (int)b[k];
-    }
-    *inside = 1;
+    for (int k = 0; k < 3; ++k) fr[k] = g[k] - fb[k];
     float q[8];
-    fld.fetch8(0, bi, q);
+    fld.fetch8(0, b, q);
     float c00 = d32_lerp(q[0], q[1], fr[0]);
     float c10 = d32_lerp(q[2], q[3], fr[0]);
     float c01 = d32_lerp(q[4], q[5], fr[0]);
@@ -250,78 +257,67 @@ __device__ __forceinline__ void march_pixel(const MarchArgs& a, const Fld& fld, 
         }
     }
 
-    // Lattice-space ray for box exits (values only, never decides a crossing).
-    float g0[3], gd[3], igd[3];
+    // Lattice-space ray for box exits (values only, never decides a crossing): the exit face
+    // along axis k is lo + far * edge (far: 1 when the ray ascends), and an axis along which the
+    // ray stands still is left far beyond every other.
+    float g0[3], igd[3], far[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
+        const float gd = dh[k] * a.inv_voxel;
         g0[k] = (o[k] - a.origin[k]) * a.inv_voxel;
-        gd[k] = dh[k] * a.inv_voxel;
-        igd[k] = gd[k] != 0.0f ? 1.0f / gd[k] : 0.0f;
+        igd[k] = gd != 0.0f ? __builtin_amdgcn_rcpf(gd) : 1e30f;
+        far[k] = gd >= 0.0f ? 1.0f : 0.0f;
     }
+    // Steps kept back before a box's exit.  A sample that overshoots the box by a fraction e of a
+    // step lies at most e / 2 voxels beyond points that are all above kBrickPositive and reads at
+    // least kBrickPositive - e, so what has to be covered is the rounding of the exit and of the
+    // sample's own position, a few 2^-24 of the coordinates; a whole step costs each box
+    // a second visit for one sample.
+    const float slack =
+        fminf(1.0f, 0.01f + 1e-6f * a.inv_h *
+                                (fmaxf(fmaxf(fabsf(o[0]), fabsf(o[1])), fabsf(o[2])) +
+                                 fmaxf(fmaxf(fabsf(a.origin[0]), fabsf(a.origin[1])), fabsf(a.origin[2])) + lam1));
 
     float Fprev = 0.0f;
-    int prev_inside = 0, prev_skipped = 0;
+    bool prev_inside = false, prev_skipped = false;
     if (s_first > 0) {
         Fprev = 1.0f;
-        prev_inside = 1;
-        prev_skipped = 1;
+        prev_inside = true;
+        prev_skipped = true;
     }
     int hit = -1;
     float Fhit = 0.0f;
-    for (int s = s_first; s <= nsteps; ++s) {
-        float g[3];
-        {
+    auto lam_of = [&](int k) {
 #pragma clang fp contract(off)
-            float kf = (float)s;
-            float lam = kf * a.h;
-            lam = lam0 + lam;
+        float lam = (float)k * a.h;
+        lam = lam0 + lam;
+        return lam;
+    };
+    float g[3], fb[3];
+    int bi[3];
+    for (int s = s_first; s <= nsteps; ++s) {
+        const bool in = locate(a, o, dh, lam_of(s), g, fb, bi);
+        float lo[3], edge;
+        if (in && fld.skip_box(bi, lo, &edge)) {
+            // Every sample whose base lies in this box is positive.
+            float lam_exit = INFINITY;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                float q = lam * dh[k];
-                q = o[k] + q;
-                q = q - a.origin[k];
-                g[k] = q * a.inv_voxel;
-            }
+            for (int k = 0; k < 3; ++k)
+                lam_exit = fminf(lam_exit, (__builtin_fmaf(edge, far[k], lo[k]) - g0[k]) * igd[k]);
+            s = max(s, min((int)((lam_exit - lam0) * a.inv_h - slack), nsteps));
+            Fprev = 1.0f;  // known positive; recomputed if it brackets the crossing
+            prev_skipped = true;
+            continue;
         }
-        {
-            const float b0 = floorf(g[0]), b1 = floorf(g[1]), b2 = floorf(g[2]);
-            if (b0 >= 0.0f && b1 >= 0.0f && b2 >= 0.0f && b0 <= (float)(a.n[0] - 2) && b1 <= (float)(a.n[1] - 2) &&
-                b2 <= (float)(a.n[2] - 2)) {
-                const int bi[3] = {(int)b0, (int)b1, (int)b2};
-                float lo[3], hi[3];
-                if (fld.skip_box(bi, lo, hi)) {
-                    // Every sample whose base lies in this box is positive.  Samples at least
-                    // one step before the ray's exit from the box are inside it (the exit and
-                    // the step count are values only: the step of margin covers their rounding).
-                    float lam_exit = INFINITY;
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        if (gd[k] > 0.0f)
-                            lam_exit = fminf(lam_exit, (hi[k] - g0[k]) * igd[k]);
-                        else if (gd[k] < 0.0f)
-                            lam_exit = fminf(lam_exit, (lo[k] - g0[k]) * igd[k]);
-                    }
-                    int s_last = (int)floorf((lam_exit - lam0) * a.inv_h) - 1;
-                    if (s_last > nsteps) s_last = nsteps;
-                    if (s_last < s) s_last = s;
-                    s = s_last;
-                    Fprev = 1.0f;  // known positive; recomputed if it brackets the crossing
-                    prev_inside = 1;
-                    prev_skipped = 1;
-                    continue;
-                }
-            }
-        }
-        int inside;
-        float F = dec_trilinear(a, fld, g, &inside);
+        const float F = in ? dec_trilinear(fld, g, fb, bi) : 1.0f;  // +1 where the stencil leaves the lattice
         if (s >= 1 && Fprev > 0.0f && F <= 0.0f) {
             hit = s;
             Fhit = F;
             break;
         }
         Fprev = F;
-        prev_inside = inside;
-        prev_skipped = 0;
+        prev_inside = in;
+        prev_skipped = false;
     }
     if (hit < 0) {
         od[pix] = 0.0f;
@@ -330,27 +326,11 @@ __device__ __forceinline__ void march_pixel(const MarchArgs& a, const Fld& fld, 
         oc[2 * HW + pix] = 0.0f;
         return;
     }
-    float la;
-    {
-#pragma clang fp contract(off)
-        float kf = (float)(hit - 1);
-        la = kf * a.h;
-        la = lam0 + la;
-    }
+    const float la = lam_of(hit - 1);
     if (prev_skipped) {
         // the bracketing sample was skipped: evaluate it (it is positive)
-        float g[3];
-        {
-#pragma clang fp contract(off)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                float q = la * dh[k];
-                q = o[k] + q;
-                q = q - a.origin[k];
-                g[k] = q * a.inv_voxel;
-            }
-        }
-        Fprev = dec_trilinear(a, fld, g, &prev_inside);
+        prev_inside = locate(a, o, dh, la, g, fb, bi);
+        Fprev = prev_inside ? dec_trilinear(fld, g, fb, bi) : 1.0f;
     }
     const float Fa = prev_inside ? Fprev : 1.0f;
     const float lam_star = la + a.h * Fa / (Fa - Fhit);
