@@ -12,7 +12,7 @@ namespace gps {
 
 constexpr int kBrick = 8;             // empty-space-skipping brick edge (lattice points)
 constexpr float kBrickPositive = 1e-3f;  // a brick whose minimum exceeds this reads positive
-constexpr int kSortCap = 8192;        // longest tile list sorted in LDS (64 KiB of keys)
+constexpr int kSortCap = 8192;        // longest tile list sorted by depth buckets
 constexpr int kRecFloats = 12;        // projected record: 48 bytes
 constexpr int kAdj = 10;              // screen-space adjoints per instance
 constexpr int kBlk = 256;             // threads per block of the per-Gaussian kernels

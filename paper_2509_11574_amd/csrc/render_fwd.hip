@@ -14,8 +14,8 @@
 //                  counts of the instances that pass the exact depth cull
 //   k_scan_tiles   one block: tile ranges
 //   k_expand<1>    the same walk: (depth, view-Gaussian) keys scattered into tile ranges
-//   k_tile_sort_*  per tile: bitonic sort of its keys in LDS (one wavefront
-//                  for tiles of <= 512 instances, a 256-lane block above)
+//   k_tile_sort_large  per tile of >= kLongTile instances: its keys by depth buckets in LDS
+//                  (shorter lists: registers of the compositing block's first wavefront)
 //   k_composite_fwd<TW,TH,B,PPT>  (composite_fwd.hip) per tile: LDS-staged
 //                  batches of B records, wavefronts skip records whose support
 //                  misses their pixels, front-to-back compositing, loss
@@ -457,9 +457,8 @@ __global__ void __launch_bounds__(kBlk) k_expand(const ViewTable* __restrict__ v
 // -------------------------------------------------------------- tile sort
 // Tiles of fewer than kLongTile keys are sorted in registers by the first
 // wavefront of their compositing block (wave_sort_tile, binning.h).
-// k_tile_sort_large: one block per longer tile (bitonic network in LDS, the
-// same compare-exchange order); tiles longer than kSortCap use the same network
-// in global memory.
+// k_tile_sort_large: one block per longer tile (depth buckets in LDS, or the bitonic network);
+// tiles longer than kSortCap use the network in global memory.
 
 __device__ __forceinline__ void cas_lds(unsigned long long* sh, int i, int j)
 {
@@ -470,39 +469,249 @@ __device__ __forceinline__ void cas_lds(unsigned long long* sh, int i, int j)
     }
 }
 
-// One block sorts the n >= kLongTile keys starting at keys[s].
-__device__ void sort_tile_block(const WsPtrs& w, unsigned int s, int n)
+// Lists of kLongTile keys and more are sorted by distributing the keys over as many buckets as
+// there are keys, following their depths (a piecewise linear map: 256 equal depth intervals,
+// each given as many buckets as it holds keys), after which a bucket holds one or two keys
+// and each key counts the smaller ones of its bucket.  About 20 LDS accesses a key, against the
+// several hundred of a network (66 steps of 2 reads and 2 writes for 2048 keys).  The map is
+// monotone in binary32, so the order is that of the keys, which are distinct.
+constexpr int kSortThreads = 512;
+constexpr int kSortLds = 4096;             // keys that meet in LDS
+constexpr unsigned int kBucketMost = 64;  // a fuller bucket (depths that coincide) sends the list to the network
+constexpr int kCoarse = 256;
+constexpr int kSortWaves = kSortThreads / 64;
+
+struct SortShared {
+    unsigned long long mid[kSortLds];      // keys by bucket
+    unsigned int fine[kSortLds / 2 + 2];   // 16-bit counts, then starts, of the n buckets
+    unsigned int coarse[kCoarse + 1];
+    unsigned int red[2][kSortWaves];
+    unsigned int cursor[2];
+};
+
+// Depth interval of a key: [z0, z0 + kCoarse / scale] cut into kCoarse.
+struct DepthMap {
+    float z0, scale;
+    __device__ float at(unsigned long long k, int& c) const
+    {
+        const float t = (__uint_as_float((unsigned int)(k >> 32)) - z0) * scale;
+        c = min((int)t, kCoarse - 1);
+        return t;
+    }
+};
+
+// The depth map of the block's keys k[0 .. n) (this lane's every kSortThreads-th) and the starts
+// of its intervals in sh.coarse.  Barriers around; sh.coarse must be zero.
+template <int PER>
+__device__ __forceinline__ DepthMap depth_intervals(const unsigned long long (&k)[PER], int n, SortShared& sh)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    unsigned int lo = 0xffffffffu, hi = 0u;  // depth bits (depths are positive: they order as the depths do)
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (tid + j * kSortThreads < n) {
+            lo = min(lo, (unsigned int)(k[j] >> 32));
+            hi = max(hi, (unsigned int)(k[j] >> 32));
+        }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (unsigned int)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (unsigned int)__shfl_xor((int)hi, o, 64));
+    }
+    if (lane == 0) {
+        sh.red[0][wid] = lo;
+        sh.red[1][wid] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) {
+        lo = min(lo, sh.red[0][q]);
+        hi = max(hi, sh.red[1][q]);
+    }
+    DepthMap map;
+    map.z0 = __uint_as_float(lo);
+    const float span = __uint_as_float(hi) - map.z0;
+    map.scale = span > 0.0f ? (float)kCoarse / span : 0.0f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (tid + j * kSortThreads < n) {
+            int c;
+            map.at(k[j], c);
+            atomicAdd(&sh.coarse[c], 1u);
+        }
+    __syncthreads();
+    if (wid == 0) {  // exclusive scan of the 256 interval counts, four to a lane
+        unsigned int v[4], sum = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = sh.coarse[4 * lane + q];
+            sum += v[q];
+        }
+        unsigned int x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        unsigned int run = x - sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            sh.coarse[4 * lane + q] = run;
+            run += v[q];
+        }
+        if (lane == 63) sh.coarse[kCoarse] = run;
+    }
+    __syncthreads();
+    return map;
+}
+
+// Sorts the n in [1, kSortLds] keys at key; false, with the keys untouched, when a bucket is too full.
+__device__ __forceinline__ bool sort_tile_buckets(unsigned long long* __restrict__ key, int n, SortShared& sh)
+{
+    constexpr int kPer = kSortLds / kSortThreads;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    unsigned long long k[kPer];  // this lane's keys
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) k[j] = tid + j * kSortThreads < n ? key[tid + j * kSortThreads] : ~0ull;
+    for (int i = tid; i <= n / 2; i += kSortThreads) sh.fine[i] = 0u;
+    if (tid <= kCoarse) sh.coarse[tid] = 0u;
+    const DepthMap map = depth_intervals<kPer>(k, n, sh);
+    unsigned int br[kPer];  // bucket << 16 | rank of arrival in it
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (j * kSortThreads >= n) break;  // uniform
+        if (tid + j * kSortThreads < n) {
+            int c;
+            const float t = map.at(k[j], c);
+            const int c0 = (int)sh.coarse[c], m = (int)sh.coarse[c + 1] - c0;
+            const unsigned int b = (unsigned int)(c0 + min((int)((t - (float)c) * (float)m), m - 1));
+            const unsigned int half = (b & 1u) * 16u;  // two 16-bit counts a word: n is below 2^16
+            const unsigned int old = atomicAdd(&sh.fine[b >> 1], 1u << half);
+            br[j] = (b << 16) | ((old >> half) & 0xffffu);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the bucket counts: a run of consecutive words to a lane
+    const int words = (n + 1) / 2, per = (words + kSortThreads - 1) / kSortThreads;
+    unsigned int sum = 0u, most = 0u;
+    for (int q = 0; q < per; ++q) {
+        const int i = tid * per + q;
+        const unsigned int v = i < words ? sh.fine[i] : 0u;
+        sum += (v & 0xffffu) + (v >> 16);
+        most = max(most, max(v & 0xffffu, v >> 16));
+    }
+    unsigned int x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) sh.red[0][wid] = x;
+    if (__syncthreads_or(most > kBucketMost)) return false;
+    unsigned int run = x - sum;
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q)
+        if (q < wid) run += sh.red[0][q];
+    for (int q = 0; q < per; ++q) {
+        const int i = tid * per + q;
+        if (i >= words) break;
+        const unsigned int v = sh.fine[i], half = run + (v & 0xffffu);
+        sh.fine[i] = run | (half << 16);
+        run = half + (v >> 16);
+    }
+    // the start past the last bucket (an odd n's is the unused half of its last word, scanned to n)
+    if (tid == 0 && (n & 1) == 0) sh.fine[n / 2] = (unsigned int)n;
+    __syncthreads();
+    auto start = [&](unsigned int b) { return (sh.fine[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu; };
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (j * kSortThreads >= n) break;
+        if (tid + j * kSortThreads < n) sh.mid[start(br[j] >> 16) + (br[j] & 0xffffu)] = k[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (j * kSortThreads >= n) break;
+        if (tid + j * kSortThreads < n) {
+            const unsigned int f0 = start(br[j] >> 16), f1 = start((br[j] >> 16) + 1u);
+            unsigned int p = f0;
+            for (unsigned int q = f0; q < f1; q += 4) {  // four independent reads at a time
+                const unsigned long long m0 = sh.mid[q], m1 = sh.mid[min(q + 1u, f1 - 1u)],
+                                         m2 = sh.mid[min(q + 2u, f1 - 1u)], m3 = sh.mid[min(q + 3u, f1 - 1u)];
+                p += (m0 < k[j] ? 1u : 0u) + (q + 1u < f1 && m1 < k[j] ? 1u : 0u) +
+                     (q + 2u < f1 && m2 < k[j] ? 1u : 0u) + (q + 3u < f1 && m3 < k[j] ? 1u : 0u);
+            }
+            key[p] = k[j];
+        }
+    }
+    return true;
+}
+
+// Splits kSortLds < n <= kSortCap keys in place, at the end of a depth interval, into two lists of at
+// most kSortLds; the length of the first, or 0 (keys untouched) when no interval ends there.
+__device__ __forceinline__ int split_tile(unsigned long long* __restrict__ key, int n, SortShared& sh)
+{
+    constexpr int kPer = kSortCap / kSortThreads;
+    const int tid = threadIdx.x;
+    unsigned long long k[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) k[j] = tid + j * kSortThreads < n ? key[tid + j * kSortThreads] : ~0ull;
+    if (tid <= kCoarse) sh.coarse[tid] = 0u;
+    if (tid < 2) sh.cursor[tid] = 0u;
+    const DepthMap map = depth_intervals<kPer>(k, n, sh);
+    // the interval starts ascend: the last one at most kSortLds opens the second list
+    int lo = 0, hi = kCoarse;
+    while (lo < hi) {
+        const int m = (lo + hi + 1) >> 1;
+        if (sh.coarse[m] <= (unsigned int)kSortLds) lo = m;
+        else hi = m - 1;
+    }
+    const int first = (int)sh.coarse[lo];
+    if (n - first > kSortLds || first == 0) return 0;  // uniform
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+        if (tid + j * kSortThreads < n) {
+            int c;
+            map.at(k[j], c);
+            const unsigned int side = c < lo ? 0u : 1u;
+            key[(side ? (unsigned int)first : 0u) + atomicAdd(&sh.cursor[side], 1u)] = k[j];
+        }
+    __syncthreads();
+    return first;
+}
+
+// Network of the lists that the buckets refuse or that are longer than kSortCap (one block).
+__device__ void sort_tile_network(const WsPtrs& w, unsigned long long* key, int n, SortShared& shared)
 {
     int P = 1;
     while (P < n) P <<= 1;
-    unsigned long long* key = w.keys + s;
-    if (n <= kSortCap) {
-        extern __shared__ unsigned long long sh[];  // kSortCap keys (dynamic LDS)
-        for (int i = threadIdx.x; i < P; i += 256) sh[i] = i < n ? key[i] : ~0ull;
+    unsigned long long* sh = shared.mid;
+    if (n <= kSortLds) {
+        for (int i = threadIdx.x; i < P; i += kSortThreads) sh[i] = i < n ? key[i] : ~0ull;
         __syncthreads();
         for (int k = 2; k <= P; k <<= 1) {
             const int half = k >> 1;
-            for (int c = threadIdx.x; c < P / 2; c += 256) {
+            for (int c = threadIdx.x; c < P / 2; c += kSortThreads) {
                 const int blk = c / half, wi = c - blk * half;
                 cas_lds(sh, blk * k + wi, blk * k + k - 1 - wi);
             }
             __syncthreads();
             for (int jj = k >> 2; jj > 0; jj >>= 1) {
-                for (int c = threadIdx.x; c < P / 2; c += 256) {
+                for (int c = threadIdx.x; c < P / 2; c += kSortThreads) {
                     const int i = (c / jj) * 2 * jj + (c % jj);
                     cas_lds(sh, i, i + jj);
                 }
                 __syncthreads();
             }
         }
-        for (int i = threadIdx.x; i < n; i += 256) key[i] = sh[i];
+        for (int i = threadIdx.x; i < n; i += kSortThreads) key[i] = sh[i];
     } else {
-        // Rare: a tile longer than the LDS holds.  Same network in global
-        // memory; elements at or past n act as +inf and are never touched.
-        if (threadIdx.x == 0) atomicAdd(&w.hdr->n_fallback, 1ull);
+        // Rare: a tile of more than kSortCap keys (counted), or one whose depths coincide and that
+        // the LDS does not hold.  Same network in global memory; elements at or past n
+        // act as +inf and are never touched.
+        if (threadIdx.x == 0 && n > kSortCap) atomicAdd(&w.hdr->n_fallback, 1ull);
         for (int k = 2; k <= P; k <<= 1) {
             const int half = k >> 1;
-            for (int c = threadIdx.x; c < P / 2; c += 256) {
+            for (int c = threadIdx.x; c < P / 2; c += kSortThreads) {
                 const int blk = c / half, wi = c - blk * half;
                 const int i = blk * k + wi, j = blk * k + k - 1 - wi;
                 if (j < n) {
@@ -515,7 +724,7 @@ __device__ void sort_tile_block(const WsPtrs& w, unsigned int s, int n)
             }
             __syncthreads();
             for (int jj = k >> 2; jj > 0; jj >>= 1) {
-                for (int c = threadIdx.x; c < P / 2; c += 256) {
+                for (int c = threadIdx.x; c < P / 2; c += kSortThreads) {
                     const int i = (c / jj) * 2 * jj + (c % jj), j = i + jj;
                     if (j < n) {
                         unsigned long long a = key[i], b = key[j];
@@ -531,16 +740,35 @@ __device__ void sort_tile_block(const WsPtrs& w, unsigned int s, int n)
     }
 }
 
-// The tiles of at least kLongTile keys lead the longest-first tile queue (the
-// tile scan counts them), so block b takes queue position b; past them, blocks
-// exit after one header read.
-__global__ void __launch_bounds__(256) k_tile_sort_large(RParams rp, WsPtrs w)
+// The tiles of at least kLongTile keys lead the longest-first tile queue (the tile scan counts
+// them); blocks stride over those positions.  A list is a chain of nine barriers and as many LDS
+// round trips, about 6 us, so what counts is how many are in flight: 42 KB of LDS and 80
+// VGPRs put three blocks of 512 lanes on a compute unit (at 151 VGPRs, one block, it took twice as
+// long).  8.5 M keys in 7360 lists of about 1150 (four 1280x720 views of 1 M Gaussians): the
+// network, with 256 lanes, 64 KB and a block per tile, took 548 us, this takes 87.
+constexpr int kSortGrid = 1024;
+
+__global__ void __launch_bounds__(kSortThreads, 6) k_tile_sort_large(RParams rp, WsPtrs w)
 {
-    if (w.hdr->n_inst > rp.cap || blockIdx.x >= w.hdr->n_large) return;
-    const int tile = (int)w.tile_queue[blockIdx.x];
-    const unsigned int s = w.tile_start[tile], e = w.tile_start[tile + 1];
-    const int n = (int)(e - s);
-    if ((unsigned int)n >= kLongTile) sort_tile_block(w, s, n);
+    __shared__ SortShared sh;
+    if (w.hdr->n_inst > rp.cap) return;
+    const unsigned int n_large = w.hdr->n_large;
+    for (unsigned int q = blockIdx.x; q < n_large; q += gridDim.x) {
+        const int tile = (int)w.tile_queue[q];
+        const unsigned int s = w.tile_start[tile], e = w.tile_start[tile + 1];
+        const int n = (int)(e - s);
+        if ((unsigned int)n < kLongTile) continue;  // uniform
+        unsigned long long* key = w.keys + s;
+        const int first = n > kSortLds && n <= kSortCap ? split_tile(key, n, sh) : 0;
+        // the whole list, or its two halves
+        for (int at = 0, len = first ? first : n; at < n; at += len, len = n - at) {
+            if (len > kSortLds || !sort_tile_buckets(key + at, len, sh)) {
+                __syncthreads();
+                sort_tile_network(w, key + at, len, sh);
+            }
+            __syncthreads();  // the next keys take this list's LDS
+        }
+    }
 }
 
 // ------------------------------------------------------------ loss reduce
@@ -679,8 +907,8 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
     if (L.nblk_vg > 0)
         GPS_LAUNCH(K_EMIT, s, k_expand<true>, dim3(L.nblk_vg * (kBlk / kExpG)), dim3(kBlk), 0, s, dvt, rp, w);
     if (rp.mode != 2)  // the unsorted sort-free blend keeps the emission order
-        GPS_LAUNCH(K_TILE_SORT_LARGE, s, k_tile_sort_large, dim3(L.n_tiles), dim3(256),
-                   kSortCap * sizeof(unsigned long long), s, rp, w);
+        GPS_LAUNCH(K_TILE_SORT_LARGE, s, k_tile_sort_large, dim3(L.n_tiles < kSortGrid ? L.n_tiles : kSortGrid),
+                   dim3(kSortThreads), 0, s, rp, w);
     if (!dispatch_cfwd(cfg, dvt, rp, w, L.n_tiles, s)) return GPS_ERR_UNSUPPORTED_CONFIG;
     GPS_LAUNCH(K_LOSS_REDUCE, s, k_loss_reduce, dim3(1), dim3(1024), 0, s, dvt, rp, w, out_loss, has_loss);
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
