@@ -63,13 +63,13 @@ __global__ void __launch_bounds__(TW * TH / PPT)
     const float invV = 1.0f / (float)rp.V;
     const float om = w.hdr->view_stats[v][2];
 
-    // Per pixel: the upstream adjoint G = (dL/dC*, dL/dD*), CG = G . (C*, D*) and
-    // the running PG = G . P_i, where P_i is the composited prefix through
-    // Gaussian i.  The remainder term of dL/dalpha_i only ever needs
-    // G . (C* - P_i) = CG - PG, so the prefix colours are not kept.
+    // Per pixel: the upstream adjoint G = (dL/dC*, dL/dD*) and CG = G . (C* - P_i, D* - ..),
+    // what remains of G . (C*, D*) behind the composited prefix P_i through Gaussian i:
+    // the remainder term of dL/dalpha_i needs nothing else, so the prefix colours are not
+    // kept.  (In the sort-free blend CG stays G . (C*, D*).)
     // thr as in the forward: -inf once a pixel has stopped for a reason other
     // than the depth test (which every deeper record fails as well).
-    float thr[PPT], T[PPT], G0[PPT], G1[PPT], G2[PPT], GD[PPT], CG[PPT], PG[PPT], invW[PPT];
+    float thr[PPT], T[PPT], G0[PPT], G1[PPT], G2[PPT], GD[PPT], CG[PPT], invW[PPT];
     // Every per-pixel load is issued before any is used, so the prologue waits for one
     // round trip: addresses outside the image are clamped to pixel 0 and an absent
     // depth plane is read from the base depth, the values then being dropped.
@@ -102,7 +102,6 @@ __global__ void __launch_bounds__(TW * TH / PPT)
             const bool dvalid = dt > 0.0f;
             thr[k] = inb[k] ? (dvalid ? dt : INFINITY) + rp.eps : -INFINITY;
             T[k] = 1.0f;
-            PG[k] = 0.0f;
             G0[k] = G1[k] = G2[k] = GD[k] = 0.0f;
             float cs0 = 0.0f, cs1 = 0.0f, cs2 = 0.0f, ds = 0.0f;
             invW[k] = 1.0f;
@@ -152,7 +151,7 @@ __global__ void __launch_bounds__(TW * TH / PPT)
                 // the instance's slot: its view-Gaussian's first slot plus this tile's
                 // place in the tile rectangle (the rectangle the expansion walked)
                 TileRect rr;
-                if (rect_of(r0.x, r0.y, r2.z, r2.w, Wd, Ht, rp.tile_w, rp.tile_h, &rr))
+                if (rect_of(r0.x, r0.y, r2.z, r2.w, Wd, Ht, TW, TH, &rr))
                     slot = o + (unsigned int)((ty - rr.ty0) * (rr.tx1 - rr.tx0 + 1) + (tx - rr.tx0));
             }
             smask[j] = mk;
@@ -174,88 +173,88 @@ __global__ void __launch_bounds__(TW * TH / PPT)
                 const int j = j0 + jw;
                 const float4 r0 = srec[3 * j], r1 = srec[3 * j + 1], r2 = srec[3 * j + 2];
                 const float c0 = r1.w, c1 = r2.x, c2 = r2.y, zi = r1.z;
-                // the forward's decisions, in the same order and arithmetic
-                bool lane_live = false, lane_use = false;  // over the lane's pixels
+                // The forward's decisions, in the same order and arithmetic, as lane masks: a
+                // lane that does not take the record takes it with opacity 0, which leaves its
+                // transmittance as it was and its adjoints zero.  Bound by VALU issue (91 % of
+                // the cycles): about 95 instructions a record and two pixels, 22 of them
+                // the reduction, against 116 with a select per update and ten products per
+                // pixel; four 1280x720 views of 1 M Gaussians 1712 -> 1540 us.
+                unsigned long long any_live = 0ull, any_use = 0ull, any_stop = 0ull;  // over the lane's pixels
                 AlphaEval ae[PPT];
                 float av[PPT], Tn[PPT];
-                bool use[PPT];
+                unsigned long long use[PPT];
 #pragma unroll
                 for (int k = 0; k < PPT; ++k) {
-                    const bool live = zi < thr[k];
-                    lane_live = lane_live || live;
+                    const unsigned long long live = mask_lt(zi, thr[k]);
+                    any_live |= live;
                     ae[k] = eval_alpha(fpx, (float)(py0 + k * Lay::LROWS), r0.x, r0.y, r0.z, r0.w, r1.x, r1.y);
+                    av[k] = MODE == 0 ? fminf(ae[k].raw, rp.amax) : ae[k].raw;
+                    use[k] = live & mask_ge(av[k], rp.amin);
+                    av[k] = mask_sel(use[k], av[k], 0.0f);
                     if (MODE == 0) {
-                        av[k] = fminf(ae[k].raw, rp.amax);
-                        const bool ok = live && av[k] >= rp.amin;
                         Tn[k] = T[k] * (1.0f - av[k]);
-                        const bool stop = ok && Tn[k] < rp.Tmin;
-                        use[k] = ok && !stop;
-                        thr[k] = stop ? -INFINITY : thr[k];
-                    } else {
-                        av[k] = ae[k].raw;
-                        Tn[k] = 0.0f;
-                        use[k] = live && av[k] >= rp.amin;
+                        any_stop |= use[k] & mask_lt(Tn[k], rp.Tmin);
                     }
-                    lane_use = lane_use || use[k];
                 }
-                const unsigned long long any_live = __builtin_amdgcn_ballot_w64(lane_live);
-                if (__builtin_amdgcn_ballot_w64(lane_use)) {
-                    // Adjoints of the contributing lanes; the others carry zero
-                    // weight, so no accumulator needs clearing.
-                    float g[kAdj];
+                // What is rare in one branch: a pixel that stops (once each), and the end of the
+                // list (an unsorted list, MODE 2, goes on): a record whose depth no lane passes.
+                if (__builtin_expect(any_stop != 0ull || (MODE != 2 && any_live == 0ull), 0)) {
+                    if (MODE == 0) {
+#pragma unroll
+                        for (int k = 0; k < PPT; ++k) {
+                            const unsigned long long stop = use[k] & mask_lt(Tn[k], rp.Tmin);
+                            av[k] = mask_sel(stop, 0.0f, av[k]);
+                            Tn[k] = mask_sel(stop, T[k], Tn[k]);
+                            thr[k] = mask_sel(stop, -INFINITY, thr[k]);
+                            use[k] &= ~stop;
+                        }
+                    }
+                    if (any_live == 0ull) {
+                        wave_alive = false;
+                        m = 0ull;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) any_use |= use[k];
+                if (any_use) {
+                    // Adjoints.  With u = dL/dalpha alpha, a lane's pixels share their column, so
+                    // the sums of u dx, u dx^2 and u dx dy follow from those of u and u dy.
+                    float u[PPT], wgt[PPT];
 #pragma unroll
                     for (int k = 0; k < PPT; ++k) {
                         const float direct = G0[k] * c0 + G1[k] * c1 + G2[k] * c2 + GD[k] * zi;  // G . (c_i, d_i)
-                        float wgt, dal;
-                        bool apath;
+                        float dal;
                         if (MODE == 0) {
-                            wgt = use[k] ? av[k] * T[k] : 0.0f;  // w_i = alpha_i T_i
-                            PG[k] = __builtin_fmaf(wgt, direct, PG[k]);
+                            wgt[k] = av[k] * T[k];  // w_i = alpha_i T_i
+                            CG[k] = __builtin_fmaf(-wgt[k], direct, CG[k]);
                             // dL/dalpha_i = T_i G.(c_i,d_i) - G.(C* - P_i) / (1 - alpha_i)
-                            dal = T[k] * direct - (CG[k] - PG[k]) * __builtin_amdgcn_rcpf(1.0f - av[k]);
-                            apath = use[k] && ae[k].raw <= rp.amax;  // a capped opacity has no gradient
-                            T[k] = use[k] ? Tn[k] : T[k];
+                            dal = __builtin_fmaf(-CG[k], __builtin_amdgcn_rcpf(1.0f - av[k]), T[k] * direct);
+                            T[k] = Tn[k];
+                            use[k] &= ~mask_gt(ae[k].raw, rp.amax);  // a capped opacity has no gradient
                         } else {
-                            wgt = use[k] ? av[k] * invW[k] : 0.0f;  // d C* / d c_i = alpha_i / (1 + W_G)
+                            wgt[k] = av[k] * invW[k];  // d C* / d c_i = alpha_i / (1 + W_G)
                             dal = invW[k] * (direct - CG[k]);
-                            apath = use[k];
                         }
                         // alpha = exp2(pw): d alpha / d pw = alpha ln 2; the constant
-                        // factors are applied once per Gaussian.
-                        const float u = apath ? dal * av[k] : 0.0f;
-                        const float t0 = u * ae[k].dx;
-                        const float t1 = u * ae[k].dy;
-                        if (k == 0) {
-                            g[0] = t0;
-                            g[1] = t1;
-                            g[2] = u * ae[k].dxx;
-                            g[3] = u * ae[k].dxy;
-                            g[4] = u * ae[k].dyy;
-                            g[5] = u;
-                            g[6] = wgt * G0[k];
-                            g[7] = wgt * G1[k];
-                            g[8] = wgt * G2[k];
-                            g[9] = wgt * GD[k];
-                        } else {
-                            g[0] += t0;
-                            g[1] += t1;
-                            g[2] = __builtin_fmaf(u, ae[k].dxx, g[2]);
-                            g[3] = __builtin_fmaf(u, ae[k].dxy, g[3]);
-                            g[4] = __builtin_fmaf(u, ae[k].dyy, g[4]);
-                            g[5] += u;
-                            g[6] = __builtin_fmaf(wgt, G0[k], g[6]);
-                            g[7] = __builtin_fmaf(wgt, G1[k], g[7]);
-                            g[8] = __builtin_fmaf(wgt, G2[k], g[8]);
-                            g[9] = __builtin_fmaf(wgt, GD[k], g[9]);
-                        }
+                        // factors are applied once per Gaussian.  (Selected, so that an
+                        // upstream adjoint that is not finite stays with the Gaussians of its pixel.)
+                        u[k] = mask_sel(use[k], dal * av[k], 0.0f);
                     }
+                    float us = u[0], uy = u[0] * ae[0].dy, uyy = u[0] * ae[0].dyy;
+                    float w0 = wgt[0] * G0[0], w1 = wgt[0] * G1[0], w2 = wgt[0] * G2[0], w3 = wgt[0] * GD[0];
+#pragma unroll
+                    for (int k = 1; k < PPT; ++k) {
+                        us += u[k];
+                        uy = __builtin_fmaf(u[k], ae[k].dy, uy);
+                        uyy = __builtin_fmaf(u[k], ae[k].dyy, uyy);
+                        w0 = __builtin_fmaf(wgt[k], G0[k], w0);
+                        w1 = __builtin_fmaf(wgt[k], G1[k], w1);
+                        w2 = __builtin_fmaf(wgt[k], G2[k], w2);
+                        w3 = __builtin_fmaf(wgt[k], GD[k], w3);
+                    }
+                    const float g[kAdj] = {us * ae[0].dx, uy, us * ae[0].dxx, uy * ae[0].dx, uyy, us, w0, w1, w2, w3};
                     wave_rows_sum10_store(g, slab + jw * kRecStride + wid * 4 * kAdj, lane);
                     written |= 1ull << jw;
-                }
-                if (MODE != 2 && !any_live) {  // this record and all deeper ones fail every pixel
-                                               // (an unsorted list, MODE 2, goes on)
-                    wave_alive = false;
-                    break;
                 }
             }
             if (lane == 0) swritten[wid] = written;
@@ -416,7 +415,7 @@ __global__ void __launch_bounds__(256) k_composite_bwd_pg(const ViewTable* __res
         // the instance's slot: its view-Gaussian's first slot plus this tile's place in
         // the tile rectangle (the rectangle the expansion walked)
         TileRect rr;
-        if (lane < kAdj && rect_of(r0.x, r0.y, r2.z, r2.w, Wd, Ht, rp.tile_w, rp.tile_h, &rr)) {
+        if (lane < kAdj && rect_of(r0.x, r0.y, r2.z, r2.w, Wd, Ht, TW, TH, &rr)) {
             const unsigned int slot =
                 w.off[vg] + (unsigned int)((ty - rr.ty0) * (rr.tx1 - rr.tx0 + 1) + (tx - rr.tx0));
             if (slot < rp.cap) w.partial[(size_t)slot * kAdj + lane] = mine;

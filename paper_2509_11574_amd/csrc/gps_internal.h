@@ -238,8 +238,11 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v)
 // reduction within rows, DPP only: the pairs (q, q+5) are exchanged between
 // lanes i and i^8 (row_ror:8), then pairs of the five results between i and
 // 7-i within each half-row (row_half_mirror), then between i and i^2 and i^1
-// (quad_perm).  Each exchange keeps one value of the pair, sends the other and
-// adds the partner's: 15 + 7 + 4 + 3 = 29 VALU operations, against 40 for ten
+// (quad_perm).  Each exchange keeps one value of the pair in a lane and adds the
+// partner lane's.  In the first two the lanes that keep the same value are whole banks
+// of four, so each is two additions that write only their banks (bank_mask), with no select;
+// in the last two a lane selects what it keeps and what it sends: 10 + 5 + 4 + 3 =
+// 22 VALU operations, against 29 with selects throughout and 40 for ten
 // independent row reductions.  Lane bits (b3 b2 b1 b0) of the row then hold
 // value (b1 ? 2 : 0) + b2 + 5 b3 when b0 = 0 and value 4 + 5 b3 when b0 = 1 (written
 // from the lanes with b1 = b2 = 0).  Every lane must be active; the summation
@@ -248,17 +251,43 @@ __device__ __forceinline__ void wave_rows_sum10_store(const float (&g)[10], floa
 {
     const int i = lane & 15;
     const bool s3 = (i & 8) != 0, s2 = (i & 4) != 0, s1 = (i & 2) != 0, s0 = (i & 1) != 0;
-    float h[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) h[q] = (s3 ? g[q + 5] : g[q]) + dpp_f<0x128>(s3 ? g[q] : g[q + 5]);  // row_ror:8
-    const float p0 = (s2 ? h[1] : h[0]) + dpp_f<0x141>(s2 ? h[0] : h[1]);  // row_half_mirror
-    const float p1 = (s2 ? h[3] : h[2]) + dpp_f<0x141>(s2 ? h[2] : h[3]);
-    const float p2 = h[4] + dpp_f<0x141>(h[4]);
+    float p0 = g[0], h1 = g[1], p1 = g[2], h3 = g[3], p2 = g[4];
+    // A DPP operand is read no sooner than two instructions after the one that writes it:
+    // the block opens with that wait, and the order below keeps it (p2, the one of its results
+    // that a DPP operand reads next, is written three from the end).
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %4, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %2, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "+&v"(p0), "+&v"(h1), "+&v"(p1), "+&v"(h3), "+&v"(p2)
+        : "v"(g[5]), "v"(g[6]), "v"(g[7]), "v"(g[8]), "v"(g[9]));
     const float r0 = (s1 ? p1 : p0) + dpp_f<0x4E>(s1 ? p0 : p1);  // quad_perm [2,3,0,1]
     const float r1 = p2 + dpp_f<0x4E>(p2);
     const float f = (s0 ? r1 : r0) + dpp_f<0xB1>(s0 ? r0 : r1);  // quad_perm [1,0,3,2]
     const int idx = s0 ? 4 + 5 * (int)s3 : (s1 ? 2 : 0) + (int)s2 + 5 * (int)s3;
     if (!s0 || (!s1 && !s2)) dst[(lane >> 4) * 10 + idx] = f;
+}
+
+// Lane masks in scalar registers: comparisons as ballots (every lane active), and a
+// select on such a mask.
+__device__ __forceinline__ unsigned long long mask_lt(float a, float b) { return __builtin_amdgcn_fcmpf(a, b, 4); }
+__device__ __forceinline__ unsigned long long mask_gt(float a, float b) { return __builtin_amdgcn_fcmpf(a, b, 2); }
+__device__ __forceinline__ unsigned long long mask_ge(float a, float b) { return __builtin_amdgcn_fcmpf(a, b, 3); }
+__device__ __forceinline__ float mask_sel(unsigned long long m, float a, float b)
+{
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? a : b;
 }
 
 // Sum over the 64 lanes, result uniform across the wave.
