@@ -61,13 +61,14 @@ static gps_status compute_layout(const gps_render_cfg* cfg, int M, const gps_cam
     if (!(cfg->alpha_min > 0.0f) || !(cfg->alpha_max > cfg->alpha_min) || !(cfg->alpha_max < 1.0f) ||
         !(cfg->z_near > 0.0f) || !(cfg->dilation > 0.0f))
         return GPS_ERR_INVALID_ARG;
-    long long n_tiles = 0, npix = 0;
+    long long n_tiles = 0, npix = 0, most_tiles = 0;
     for (int v = 0; v < V; ++v) {
         if (!cam_ok(cams[v])) return GPS_ERR_INVALID_ARG;
         const long long tx = (cams[v].width + cfg->tile_w - 1) / cfg->tile_w;
         const long long ty = (cams[v].height + cfg->tile_h - 1) / cfg->tile_h;
         if (tx > 65534 || ty > 65534) return GPS_ERR_INVALID_ARG;
         n_tiles += tx * ty;
+        most_tiles = std::max(most_tiles, tx * ty);
         npix += (long long)cams[v].width * cams[v].height;
     }
     const long long nvg = (long long)V * M;
@@ -77,9 +78,9 @@ static gps_status compute_layout(const gps_render_cfg* cfg, int M, const gps_cam
     if (cap >= 0xffffffffull) return GPS_ERR_INVALID_ARG;
     L->n_tiles = (int)n_tiles;
     L->nvg = (int)nvg;
-    L->nblk_vg = (int)((nvg + kBlk - 1) / kBlk);
     L->nblk_g = (M + kBlk - 1) / kBlk;
     L->cap = cap;
+    L->bin = bin_shape(M, V, (size_t)n_tiles, (size_t)most_tiles, cap);
     size_t o = 0;
     L->hdr = o;
     o = align_up(o + 1024);
@@ -88,7 +89,7 @@ static gps_status compute_layout(const gps_render_cfg* cfg, int M, const gps_cam
     L->tilemax = o;
     o = align_up(o + 4 * (size_t)n_tiles);
     L->tile_cnt = o;
-    o = align_up(o + 4 * (size_t)kCntSplit * n_tiles);
+    o = align_up(o + 4 * (size_t)n_tiles);
     L->tile_start = o;
     o = align_up(o + 4 * (size_t)(n_tiles + 1));
     L->tile_queue = o;
@@ -101,18 +102,22 @@ static gps_status compute_layout(const gps_render_cfg* cfg, int M, const gps_cam
     o = align_up(o + 4 * (size_t)npix);
     L->rec = o;
     o = align_up(o + 4 * kRecFloats * (size_t)nvg);
-    L->cnt = o;
+    L->span = o;
     o = align_up(o + 4 * (size_t)nvg);
     L->off = o;
     o = align_up(o + 4 * (size_t)nvg);
-    L->blk_sum = o;
-    o = align_up(o + 4 * (size_t)L->nblk_vg);
-    L->blk_off = o;
-    o = align_up(o + 4 * (size_t)L->nblk_vg);
+    L->kept = o;
+    o = align_up(o + 4 * (size_t)nvg);
+    L->depth = o;
+    o = align_up(o + 4 * (size_t)nvg);
+    L->seg_sum = o;
+    o = align_up(o + 4 * (size_t)kMostSegs);
+    L->seg_off = o;
+    o = align_up(o + 4 * (size_t)kMostSegs);
     L->keys = o;
     o = align_up(o + 8 * (size_t)cap);
-    L->inst_vg = o;
-    o = align_up(o + 4 * (size_t)cap);
+    L->tile_rows = o;
+    o = align_up(o + 4 * std::max((size_t)cap, kCntSplit * (size_t)n_tiles));
     L->partial = o;
     o = align_up(o + 4 * (size_t)kAdj * cap);
     L->pose_part = o;

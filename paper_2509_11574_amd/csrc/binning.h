@@ -2,16 +2,69 @@
 // Kept apart from the headers of the compositing kernels, which they do not affect.
 #pragma once
 
+#include <algorithm>
+
 #include "gps_internal.h"
 
 namespace gps {
 
-constexpr int kExpG = 64;             // view-Gaussians per block of the instance expansion (kBlk lanes walk
-                                      // their tile rectangles: about kBlk / kExpG lanes per Gaussian)
-constexpr int kExpGLog2 = 6;
-static_assert((1 << kExpGLog2) == kExpG && kBlk % kExpG == 0, "expansion share");
-constexpr int kCntSplit = 4;          // sub-counters per tile for the count pass's atomics (block index mod 4):
-                                      // fewer increments queue on one address
+// The projection counts the instances of its Gaussians per tile and the emission gives each
+// a place, both in blocks over a share of one view's Gaussians.  A block's counters are in LDS and
+// its counts a row of their own in memory, so neither pass has an atomic that leaves the CU:
+// at four 1280x720 views of 1 M Gaussians (8.5 M instances) the atomics on counters shared by
+// all blocks alone took 370 us, and the whole binning 747 against 245 now.
+constexpr int kBinTiles = 12288;      // most tiles of a view with counters in LDS (48 KB a block: 64 with the walk)
+constexpr int kCntSplit = 4;          // beyond, rows in memory that the blocks of a view share: 1 M Gaussians
+                                      // in 12384 tiles 282 us, in 12288 with LDS 222
+constexpr int kKeptBits = 32;         // slots of a Gaussian whose culls are kept as bits
+
+// The shapes of a block (wavefronts, Gaussians a wavefront takes at a time), always 256 Gaussians:
+//   few Gaussians:  8 of 32.  The walk of the slots is what takes long (up to 20 slots a
+//                   Gaussian with 8x8 tiles), so it gets twice the wavefronts although the
+//                   projection then uses half their lanes.  The binning of 50 k Gaussians of 14 slots
+//                   takes 103 us, of 100 k of 3 slots 28; with 4 of 64 128 and 29, with 16 of 16
+//                   87 and 35.
+//   many:           4 of 64, which fill the chip: 8 wavefronts a SIMD.  (16 of 64, for fewer
+//                   rows, measured the same.)
+constexpr int kFewWaves = 8, kFewPer = 32, kManyWaves = 4, kManyPer = 64;
+constexpr long long kFewGaussians = 131072;  // over the views
+constexpr int kMostWaves = 8192;             // over the views
+constexpr int kMostSegs = kMostWaves;
+static_assert(kFewGaussians / kFewPer + GPS_MAX_VIEWS * kFewWaves <= kMostSegs, "a view's last block may be short");
+constexpr size_t kMostRowWords = 4u << 20;   // of tile counts over all blocks (12288 tiles: 341 blocks)
+
+// Gaussians of a map lie in memory by the surface that they were seeded on, so the ones in view are
+// runs of thousands.  A wavefront therefore takes its share from all over the map: with
+// consecutive Gaussians the longest walk is five times the mean, and projection and emission of four
+// 1280x720 views of 1 M take 116 + 144 us against 87 + 126.  Long runs, whose loads are whole
+// lines, where a wavefront takes several anyway.
+constexpr int kRunFew = 8, kRunShort = 16, kRunLong = 64, kRunIters = 4;
+
+inline BinShape bin_shape(int M, int V, size_t n_tiles, size_t most_tiles, unsigned long long cap)
+{
+    BinShape b{0, kManyWaves, kManyPer, 0, kRunLong, 0, 0, 0};
+    if (M == 0) return b;
+    const bool few = (long long)M * V <= kFewGaussians;
+    // The rows lie where the instance capacity has left room.  With much less room than blocks
+    // wanted, the shared rows.
+    const unsigned long long room = std::min(cap, (unsigned long long)std::max(kMostRowWords, 64 * n_tiles)) / n_tiles;
+    b.lds = most_tiles <= (size_t)kBinTiles && room >= (unsigned long long)std::min((M + kBlk - 1) / kBlk, 64);
+    if (few) {
+        b.waves = kFewWaves;
+        b.per = kFewPer;
+    }
+    const int group = b.waves * b.per, wanted = (M + group - 1) / group;
+    int most = few ? wanted : std::max(kMostWaves / b.waves / V, 1);
+    if (b.lds) most = (int)std::min((unsigned long long)most, room);
+    b.iters = (wanted + most - 1) / most;
+    b.chunks = (wanted + b.iters - 1) / b.iters;
+    b.run = b.iters >= kRunIters ? kRunLong : kRunShort;
+    if (few) b.run = kRunFew;
+    b.rows = b.lds ? b.chunks : kCntSplit;
+    b.lds_words = b.lds ? (int)most_tiles : 0;
+    return b;
+}
+
 constexpr int kSmallSort = 512;       // one wavefront sorts up to this many keys in registers
 // Tiles of at least kLongTile keys (exactly those whose queue bucket floor(log2(n + 1))
 // is log2(kSmallSort) or more, so they lead the longest-first queue) take the block sort.

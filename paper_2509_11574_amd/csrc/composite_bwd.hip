@@ -134,6 +134,7 @@ __global__ void __launch_bounds__(TW * TH / PPT)
     const unsigned int s = w.tile_start[tile], e = w.tile_start[tile + 1];
     const int tx0 = tx * TW, ty0 = ty * TH;
     bool wave_alive = true;  // some pixel of this wavefront still takes records
+    unsigned int done = s;   // records whose slots are written
     for (unsigned int b = s; b < e; b += B) {
         if (__syncthreads_count(wave_alive && lane == 0) == 0) break;
         for (int j = threadIdx.x; j < B; j += NT) {
@@ -273,8 +274,23 @@ __global__ void __launch_bounds__(TW * TH / PPT)
                 if (slot < rp.cap) w.partial[(size_t)slot * kAdj + q] = acc;
             }
             __syncthreads();
+            done = b + (unsigned int)j1;
         }
         if (!alive_now) break;
+    }
+    // The records behind the last pixel's stop have no adjoint: their slots are zeroed here
+    // (the per-Gaussian sum reads the slot of every instance).
+    for (unsigned int j = done + threadIdx.x; j < e; j += NT) {
+        const unsigned int vg = (unsigned int)w.keys[j];
+        if (vg >= (unsigned int)rp.nvg) continue;
+        const float4 r0 = w.rec[3 * (size_t)vg], r2 = w.rec[3 * (size_t)vg + 2];
+        TileRect rr;
+        if (!rect_of(r0.x, r0.y, r2.z, r2.w, Wd, Ht, TW, TH, &rr)) continue;
+        const unsigned int slot = w.off[vg] + (unsigned int)((ty - rr.ty0) * (rr.tx1 - rr.tx0 + 1) + (tx - rr.tx0));
+        if (slot < rp.cap) {
+#pragma unroll
+            for (int q = 0; q < kAdj; ++q) w.partial[(size_t)slot * kAdj + q] = 0.0f;
+        }
     }
 }
 

@@ -93,32 +93,43 @@ struct WsHeader {
     float view_stats[GPS_MAX_VIEWS][4];  // per view: colour L1 sum, depth L1 sum, |Omega|, pad
 };
 
+// How the projection and the emission share the view-Gaussians: `chunks` blocks of `waves`
+// wavefronts per view, a wavefront taking `per` Gaussians `iters` times, as runs of `run`
+// consecutive ones (see binning.h).  With `lds` a block counts its instances per tile in LDS
+// (`lds_words` counters) and has a row of tile counts of its own (rows = chunks); otherwise
+// the blocks of a view share `rows` rows in memory.
+struct BinShape {
+    int chunks, waves, per, iters, run, rows, lds, lds_words;
+};
+
 struct WsLayout {
     size_t total;
-    size_t hdr, vtab, tilemax, tile_cnt, tile_start, tile_queue, tile_loss, tile_pairs, pix_aux, rec, cnt, off,
-        blk_sum, blk_off,
-        keys, inst_vg, partial, pose_part;
-    int n_tiles, nvg, nblk_vg, nblk_g;
+    size_t hdr, vtab, tilemax, tile_cnt, tile_start, tile_queue, tile_loss, tile_pairs, pix_aux, rec, span, off,
+        kept, depth, seg_sum, seg_off,
+        keys, tile_rows, partial, pose_part;
+    int n_tiles, nvg, nblk_g;
+    BinShape bin;
     unsigned long long cap;
 };
 
 struct WsPtrs {
     WsHeader* hdr;
     float* tilemax;
-    unsigned int* tile_cnt;     // [kCntSplit][n_tiles]: instances that pass the depth cull, per sub-counter;
-                                // after the tile scan, the start of each sub-counter's range
+    unsigned int* tile_cnt;     // [n_tiles]: instances that pass the culls
     unsigned int* tile_start;   // n_tiles + 1
     unsigned int* tile_queue;   // tiles in processing order (longest first)
     float4* tile_loss;          // per tile: colour L1 sum, depth L1 sum, |Omega| count, 0
     uint2* tile_pairs;          // per tile: evaluated and composited (pixel, instance) pairs
     float* pix_aux;             // per pixel: T_final (sorted) or W_G (sort-free)
-    float4* rec;                // 3 float4 per view-Gaussian
-    unsigned int* cnt;
-    unsigned int* off;
-    unsigned int* blk_sum;
-    unsigned int* blk_off;
+    float4* rec;                // 3 float4 per view-Gaussian (written where span is not 0)
+    unsigned int* span;         // per view-Gaussian: tiles of its rectangle, width | height << 16; 0: not seen
+    unsigned int* off;          // per view-Gaussian: first tile x | y << 16 (projection), then its first slot (emission)
+    unsigned int* kept;         // per view-Gaussian of at most kKeptBits slots: bit k = slot k passed the culls
+    float* depth;               // per view-Gaussian: depth key
+    unsigned int* seg_sum;      // per wavefront of the projection: slots of its Gaussians
+    unsigned int* seg_off;      // and the first of them
     unsigned long long* keys;   // (depth bits << 32) | view-Gaussian, grouped by tile
-    unsigned int* inst_vg;      // per slot: the instance's rank in its tile sub-counter (count -> emit)
+    unsigned int* tile_rows;    // per view [rows][tiles]: instances per (row, tile), then their first place in the tile
     float* partial;             // [cap][kAdj]
     float* pose_part;           // [nblk_g][V][6]
 };
@@ -135,12 +146,14 @@ inline WsPtrs ws_ptrs(char* ws, const WsLayout& L)
     p.tile_pairs = reinterpret_cast<uint2*>(ws + L.tile_pairs);
     p.pix_aux = reinterpret_cast<float*>(ws + L.pix_aux);
     p.rec = reinterpret_cast<float4*>(ws + L.rec);
-    p.cnt = reinterpret_cast<unsigned int*>(ws + L.cnt);
+    p.span = reinterpret_cast<unsigned int*>(ws + L.span);
     p.off = reinterpret_cast<unsigned int*>(ws + L.off);
-    p.blk_sum = reinterpret_cast<unsigned int*>(ws + L.blk_sum);
-    p.blk_off = reinterpret_cast<unsigned int*>(ws + L.blk_off);
+    p.kept = reinterpret_cast<unsigned int*>(ws + L.kept);
+    p.depth = reinterpret_cast<float*>(ws + L.depth);
+    p.seg_sum = reinterpret_cast<unsigned int*>(ws + L.seg_sum);
+    p.seg_off = reinterpret_cast<unsigned int*>(ws + L.seg_off);
     p.keys = reinterpret_cast<unsigned long long*>(ws + L.keys);
-    p.inst_vg = reinterpret_cast<unsigned int*>(ws + L.inst_vg);
+    p.tile_rows = reinterpret_cast<unsigned int*>(ws + L.tile_rows);
     p.partial = reinterpret_cast<float*>(ws + L.partial);
     p.pose_part = reinterpret_cast<float*>(ws + L.pose_part);
     return p;

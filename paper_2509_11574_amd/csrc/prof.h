@@ -14,7 +14,6 @@ enum KernelId {
     K_TILEMAX,
     K_PROJECT,
     K_SCAN,
-    K_TILE_COUNT,
     K_SCAN_TILES,
     K_EMIT,
     K_TILE_SORT,

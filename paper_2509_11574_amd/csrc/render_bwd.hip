@@ -12,6 +12,7 @@
 //   the Adam step to its Gaussian and k_pose_reduce advances the step counter.
 // No floating-point atomics: results are bitwise reproducible.
 #include "adam_math.h"
+#include "binning.h"
 #include "launch.h"
 #include "prof.h"
 #include "render_common.h"
@@ -20,7 +21,7 @@
 namespace gps {
 
 // ------------------------------------------------------------- gauss bwd
-constexpr unsigned int kCoopSlots = 32;  // more slots than this: summed by the whole wavefront
+constexpr unsigned int kCoopSlots = kKeptBits;  // more slots than this: summed by the whole wavefront
 constexpr unsigned int kSlotGroup = 8;   // slots loaded together by one lane
 
 // EWA chain rule of one Gaussian in one view.  The summed instance partials are
@@ -70,7 +71,7 @@ __global__ void __launch_bounds__(kBlk) k_gauss_bwd(const ViewTable* __restrict_
     // waited for: the slot count and offset of the first view, the Adam state of the
     // five parameter groups (14 scalars) and the parameters.  The slot sums then wait
     // for one round trip, and the Adam loads overlap them.
-    const unsigned int cnt0 = live ? w.cnt[g] : 0u, off0 = live ? w.off[g] : 0u;
+    const unsigned int span0 = live ? w.span[g] : 0u, off0 = live ? w.off[g] : 0u, kept0 = live ? w.kept[g] : 0u;
     constexpr int kAdamRows[5] = {3, 3, 4, 1, 3};
     float ap[14], am[14], av[14];
     const bool adam_here = live && af.on && !over;
@@ -134,13 +135,14 @@ __global__ void __launch_bounds__(kBlk) k_gauss_bwd(const ViewTable* __restrict_
     for (int v = 0; v < vt.n; ++v) {
         float pose[6] = {0, 0, 0, 0, 0, 0};
         const size_t vg = (size_t)v * M + g;
-        const unsigned int cl = v == 0 ? cnt0 : (live ? w.cnt[vg] : 0u);
+        const unsigned int span = v == 0 ? span0 : (live ? w.span[vg] : 0u);
         const unsigned int ol = v == 0 ? off0 : (live ? w.off[vg] : 0u);
-        unsigned int cnt = over ? 0u : cl;
+        unsigned int kept = v == 0 ? kept0 : (live ? w.kept[vg] : 0u);
+        unsigned int cnt = over ? 0u : (span & 0xffffu) * (span >> 16);
         const unsigned int o = cnt ? ol : 0u;
         if ((unsigned long long)o + cnt > w.hdr->n_inst) cnt = 0u;  // guard: stay inside the emitted slots
-        // Slots of tiles removed by the depth cull were zeroed by the emission, so the
-        // whole contiguous range is summed (in a fixed order).
+        // The slots are summed in order, of up to kKeptBits those whose instance passed the
+        // culls (the others hold nothing); of more, all (the emission zeroed the others).
         float A[kAdj];
 #pragma unroll
         for (int q = 0; q < kAdj; ++q) A[q] = 0.0f;
@@ -168,16 +170,18 @@ __global__ void __launch_bounds__(kBlk) k_gauss_bwd(const ViewTable* __restrict_
         }
         if (cnt > 0 && cnt <= kCoopSlots) {
             // The lane's slots in groups of kSlotGroup: the loads of a group are issued
-            // together, so a group costs one round trip (a position past the count reads
-            // the group's first slot again and adds zero); the slots are still added in
-            // order (adding +0.0 to a sum that starts at +0.0 leaves it unchanged).
+            // together, so a group costs one round trip (a place past the last reads
+            // the group's first slot again and adds zero; adding +0.0 to a sum that starts at
+            // +0.0 leaves it unchanged).
             const float* part = w.partial + (size_t)o * kAdj;
-            for (unsigned int k0 = 0; k0 < cnt; k0 += kSlotGroup) {
+            while (kept) {
                 float sv[kSlotGroup][kAdj];
+                const unsigned int k0 = (unsigned int)__builtin_ctz(kept);
 #pragma unroll
                 for (unsigned int i = 0; i < kSlotGroup; ++i) {
-                    const bool has = k0 + i < cnt;
-                    const float* ps = part + (size_t)(has ? k0 + i : k0) * kAdj;
+                    const bool has = kept != 0u;
+                    const float* ps = part + (size_t)(has ? (unsigned int)__builtin_ctz(kept) : k0) * kAdj;
+                    kept &= kept - 1u;
 #pragma unroll
                     for (int q = 0; q < kAdj; ++q) sv[i][q] = ps[q];
 #pragma unroll

@@ -25,29 +25,38 @@ struct GGrads {
     float* sh;
 };
 
+// The SH bands of K coefficients per channel at the unit direction d, added to col.  The
+// coefficients of all channels are in flight together (the count is a compile-time one).
+template <int K>
+__device__ __forceinline__ void add_bands(const GParams& gp, int M, int g, float d0, float d1, float d2, float col[3])
+{
+    float c[3 * K], Y[K];
+#pragma unroll
+    for (int k = 0; k < 3 * K; ++k) c[k] = gp.sh[(size_t)k * M + g];
+    sh_basis<K>(d0, d1, d2, Y);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+        for (int k = 0; k < K; ++k) col[ch] += c[ch * K + k] * Y[k];
+}
+
 // The colour of Gaussian g seen from camera c: rgb plus the SH bands at the unit
-// direction from the camera centre o = -R^T t to the centre mu.
+// direction from the camera centre o = -R^T t to the centre mu.  SH: there are bands.
+template <bool SH>
 __device__ __forceinline__ void view_colour(const GParams& gp, int M, int g, const DevCam& c, float m0, float m1,
                                             float m2, float col[3])
 {
     col[0] = gp.rgb[g];
     col[1] = gp.rgb[M + g];
     col[2] = gp.rgb[2 * M + g];
-    if (gp.sh_k == 0) return;
+    if (!SH) return;
     const float v0 = m0 + (c.R[0] * c.t[0] + c.R[3] * c.t[1] + c.R[6] * c.t[2]);
     const float v1 = m1 + (c.R[1] * c.t[0] + c.R[4] * c.t[1] + c.R[7] * c.t[2]);
     const float v2 = m2 + (c.R[2] * c.t[0] + c.R[5] * c.t[1] + c.R[8] * c.t[2]);
     const float ir = 1.0f / sqrtf(v0 * v0 + v1 * v1 + v2 * v2);
-    float Y[kShMaxK];
-    if (gp.sh_k == 15) sh_basis<15>(v0 * ir, v1 * ir, v2 * ir, Y);
-    else if (gp.sh_k == 8) sh_basis<8>(v0 * ir, v1 * ir, v2 * ir, Y);
-    else sh_basis<3>(v0 * ir, v1 * ir, v2 * ir, Y);
-    const int K = gp.sh_k;
-    for (int ch = 0; ch < 3; ++ch) {
-        float acc = col[ch];
-        for (int k = 0; k < K; ++k) acc += gp.sh[((size_t)ch * K + k) * M + g] * Y[k];
-        col[ch] = acc;
-    }
+    if (gp.sh_k == 15) add_bands<15>(gp, M, g, v0 * ir, v1 * ir, v2 * ir, col);
+    else if (gp.sh_k == 8) add_bands<8>(gp, M, g, v0 * ir, v1 * ir, v2 * ir, col);
+    else add_bands<3>(gp, M, g, v0 * ir, v1 * ir, v2 * ir, col);
 }
 
 // Block-wide exclusive scan of one unsigned per thread (NT a multiple of 64).
@@ -151,6 +160,11 @@ struct SupportTest {
         kx = -0.5f * B * __builtin_amdgcn_rcpf(A);
         ky = -0.5f * B * __builtin_amdgcn_rcpf(C);
         need = (l2amin - r1.y) * 1.0001f - 1e-4f;  // log2(alpha_min / sigma), with slack
+    }
+    // From the values of a test made before: (mx, my, A, B), (C, kx, ky, need).
+    __device__ SupportTest(const float4& a, const float4& b)
+        : mx(a.x), my(a.y), A(a.z), B(a.w), C(b.x), kx(b.y), ky(b.z), need(b.w)
+    {
     }
     __device__ float at(float dx, float dy) const { return dx * (A * dx + B * dy) + C * dy * dy; }
     __device__ bool meets(float x0, float y0, float w, float h) const

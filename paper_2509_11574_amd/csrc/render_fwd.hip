@@ -6,14 +6,12 @@
 // so the sequence is graph-capturable):
 //   k_tilemax      per screen tile: max of the SDF depth (invalid = +inf); launched
 //                  with the view-table upload, not per forward
-//   k_project      per (view, Gaussian): projected record and the number of
-//                  screen tiles its support box covers (one slot per tile);
-//                  also clears the per-tile counters of this forward
-//   k_scan_blocks  one block: offsets of the per-block slot counts
-//   k_expand<0>    block-cooperative walk of the tile rectangles: per-tile
-//                  counts of the instances that pass the exact depth cull
+//   k_project      per (view, Gaussian): projected record, the number of screen tiles its
+//                  support box covers (one slot per tile), and per block and tile the
+//                  count of the instances that pass the exact culls
+//   k_scan_rows    per tile: each block's first place; one block: the slots' numbers
 //   k_scan_tiles   one block: tile ranges
-//   k_expand<1>    the same walk: (depth, view-Gaussian) keys scattered into tile ranges
+//   k_emit         (depth, view-Gaussian) keys scattered into tile ranges
 //   k_tile_sort_large  per tile of >= kLongTile instances: its keys by depth buckets in LDS
 //                  (shorter lists: registers of the compositing block's first wavefront)
 //   k_composite_fwd<TW,TH,B,PPT>  (composite_fwd.hip) per tile: LDS-staged
@@ -55,19 +53,6 @@ __global__ void __launch_bounds__(256) k_tilemax(const ViewTable* __restrict__ v
     if (threadIdx.x == 0) w.tilemax[tile] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// Per-forward resets (run by the first kernel of the forward, over its whole
-// grid): the per-tile sub-counters and the forward's header counters.
-__device__ __forceinline__ void forward_resets(const ViewTable& vt, const RParams& rp, const WsPtrs& w)
-{
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x, nth = gridDim.x * blockDim.x;
-    for (int i = gid; i < kCntSplit * vt.n_tiles; i += nth) w.tile_cnt[i] = 0u;
-    if (gid == 0) {
-        w.hdr->n_inst = 0ull;
-        w.hdr->n_fallback = 0ull;
-        w.hdr->n_views = rp.V;
-    }
-}
-
 // ---------------------------------------------------------------- project
 // EWA projection of one Gaussian into one view (Eq. 3; 3DGS convention):
 //   p_c = R mu + t, Sigma_3D = R_q diag(s^2) R_q^T, J the pinhole Jacobian,
@@ -85,6 +70,7 @@ struct ProjOut {
     bool valid;
 };
 
+template <bool SH>
 __device__ __forceinline__ ProjOut project_one(const DevView& V, const RParams& rp, const GParams& gp, int g)
 {
     ProjOut o;
@@ -156,301 +142,529 @@ __device__ __forceinline__ ProjOut project_one(const DevView& V, const RParams& 
     constexpr float kL2E = 1.4426950408889634f;
     o.r0 = make_float4(mx, my, (-0.5f * kL2E) * (C * idet), kL2E * (B * idet));
     float col[3];
-    view_colour(gp, M, g, c, m0, m1, m2, col);
+    view_colour<SH>(gp, M, g, c, m0, m1, m2, col);
     o.r1 = make_float4((-0.5f * kL2E) * (A * idet), __log2f(sig), z, col[0]);
     o.r2 = make_float4(col[1], col[2], rxp, ryp);
     o.valid = true;
     return o;
 }
 
-__global__ void __launch_bounds__(kBlk) k_project(const ViewTable* __restrict__ vtp, RParams rp, GParams gp, WsPtrs w)
+// ------------------------------------------------- walk of the tile rectangles
+// A wavefront takes PER Gaussians of one view (a lane each) and its lanes then walk the
+// concatenation of their tile rectangles together, 64 slots at a time, so a large
+// Gaussian, or a run of dense ones, is spread over lanes instead of serialising one.
+// The Gaussians that are seen stand in LDS without gaps; the slots at which they start
+// are set in a 64-bit word per window, and the owner of a slot is the number of starts
+// up to it.  Slots are numbered per wavefront in walking order from seg_off.
+template <int PER>
+struct WaveWalk {
+    unsigned long long starts;
+    uint4 c[PER];  // depth bits, first slot, first tile (x | y << 16), width | lane << 16 | big << 31
+};
+
+template <int PER>
+struct CountWalk : WaveWalk<PER> {
+    float4 a[PER];  // mx, my, A, B of the support test
+    float4 b[PER];  // C, kx, ky, need
+};
+
+template <int PER>
+struct EmitWalk : WaveWalk<PER> {
+    unsigned int kept[PER];
+};
+
+// LDS words of one wavefront, written and read by its own lanes: order without a barrier.
+__device__ __forceinline__ void wave_lds_order()
 {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inclusive sum over the lanes before and at this one.
+__device__ __forceinline__ unsigned int wave_incl_sum(unsigned int x)
+{
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
+__device__ __forceinline__ unsigned int lanes_before(unsigned long long m)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+}
+
+// The Gaussian of a lane in iteration i of a wavefront's share (M: none).
+template <int PER>
+__device__ __forceinline__ int share_gaussian(const BinShape& bs, int chunk, int wid, int lane, int i, int M)
+{
+    if (lane >= PER) return M;
+    const unsigned int per = (unsigned int)(PER / bs.run);  // runs a wavefront takes at a time
+    const unsigned long long waves = (unsigned long long)bs.chunks * bs.waves;
+    const unsigned long long r = ((unsigned long long)i * per + (unsigned int)(lane / bs.run)) * waves +
+                                 (unsigned int)(chunk * bs.waves + wid);
+    const unsigned long long g = r * bs.run + (unsigned int)(lane % bs.run);
+    return g < (unsigned long long)M ? (int)g : M;
+}
+
+// The slots of the window [w0, w0 + 64) of a walk: for this lane's slot its owner in the
+// wavefront's list.  n: this lane's slots (0: its Gaussian is not seen), excl: its first;
+// before: seen Gaussians that start before the window (advanced by those that start in it).
+template <int PER>
+__device__ __forceinline__ unsigned int walk_owner(WaveWalk<PER>& ww, unsigned int n, unsigned int excl, unsigned int w0,
+                                                   unsigned int& before)
+{
+    const int lane = threadIdx.x & 63;
+    wave_lds_order();
+    if (lane == 0) ww.starts = 0ull;
+    wave_lds_order();
+    if (n > 0u && excl - w0 < 64u) atomicOr(&ww.starts, 1ull << (excl - w0));
+    wave_lds_order();
+    const unsigned long long st = ww.starts;
+    const unsigned int lo = (unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)st);
+    const unsigned int hi = (unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)(st >> 32));
+    const unsigned long long s = ((unsigned long long)hi << 32) | lo;
+    const unsigned int owner = before + lanes_before(s) + (unsigned int)((s >> lane) & 1ull) - 1u;
+    before += (unsigned int)__builtin_popcountll(s);
+    return owner;
+}
+
+// Row and column of slot j in a rectangle `width` tiles wide.  Below 2^21 slots (always with
+// counters in LDS: a view then has at most kBinTiles tiles) the product with the reciprocal is
+// off by less than j 2^-22 / width < 0.5 / width, so the truncation is exact.
+template <bool LDS>
+__device__ __forceinline__ unsigned int slot_row(unsigned int j, unsigned int width)
+{
+    static_assert(kBinTiles <= (1 << 20), "slot numbers are exact in the reciprocal form");
+    if (LDS) return (unsigned int)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)width));
+    return j / width;
+}
+
+// One slot of the walk: its tile, and whether the instance passes the culls: the support
+// ellipse meets the tile (its box may only overlap it), and the exact tile-level depth cull.
+struct Slot {
+    unsigned int j, tile;  // in the rectangle, in the view
+    bool small;            // of a Gaussian whose culls are kept as bits
+};
+
+template <bool LDS>
+__device__ __forceinline__ Slot slot_of(const uint4& c, unsigned int i, int tiles_x, int* tx, int* ty)
+{
+    Slot s;
+    s.j = i - c.y;
+    const unsigned int width = c.w & 0xffffu, q = slot_row<LDS>(s.j, width);
+    *tx = (int)((c.z & 0xffffu) + (s.j - q * width));
+    *ty = (int)((c.z >> 16) + q);
+    s.tile = (unsigned int)(*ty * tiles_x + *tx);
+    s.small = (int)c.w >= 0;
+    return s;
+}
+
+__device__ __forceinline__ bool slot_passes(const SupportTest& st, float z, int tx, int ty, float tile_max,
+                                            const RParams& rp)
+{
+    return st.meets((float)(tx * rp.tile_w), (float)(ty * rp.tile_h), (float)rp.tile_w, (float)rp.tile_h) &&
+           z < tile_max + rp.eps;
+}
+
+// ---------------------------------------------------------------- project
+// Projection of a share of one view's Gaussians (see binning.h), the number of slots of
+// each (tiles of its rectangle), and the walk that counts the instances per tile: those that
+// pass the culls, kept as a bit per slot for the emission and the backward.  Bound by latency
+// for few Gaussians (100 k at 1280x720: 9 us, with a pass of its own for the counts 6 + 5 + 11) and by
+// the walk's instructions for many (4 x 1 M: 87 us against 68 + 11 + 370).
+template <int WAVES, int PER, bool LDS, bool SH>
+__global__ void __launch_bounds__(64 * WAVES, 4) k_project(const ViewTable* __restrict__ vtp, RParams rp, BinShape bs,
+                                                     GParams gp, WsPtrs w)
+{
+    extern __shared__ unsigned int counter[];  // LDS: per tile of the view
+    __shared__ CountWalk<PER> walk[WAVES];
     const ViewTable& vt = *vtp;
-    forward_resets(vt, rp, w);
-    const int vg = blockIdx.x * kBlk + threadIdx.x;
-    unsigned int count = 0;
-    if (vg < rp.nvg) {
-        const int v = vg / rp.M, g = vg - v * rp.M;
-        const DevView& V = vt.v[v];
-        ProjOut p = project_one(V, rp, gp, g);
-        w.rec[3 * (size_t)vg + 0] = p.r0;
-        w.rec[3 * (size_t)vg + 1] = p.r1;
-        w.rec[3 * (size_t)vg + 2] = p.r2;
-        TileRect r;
-        if (p.valid && rect_of(p.r0.x, p.r0.y, p.r2.z, p.r2.w, V.cam.W, V.cam.H, rp.tile_w, rp.tile_h, &r))
-            count = (unsigned int)((r.tx1 - r.tx0 + 1) * (r.ty1 - r.ty0 + 1));  // one slot per covered tile
-        w.cnt[vg] = count;
+    const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
+    const DevView& V = vt.v[v];
+    const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
+    CountWalk<PER>& ww = walk[wid];
+    const float l2amin = __log2f(rp.amin);
+    if (LDS) {
+        for (int t = threadIdx.x; t < n_tiles; t += 64 * WAVES) counter[t] = 0u;
+        __syncthreads();
     }
-    unsigned int tot;
-    block_excl_scan<kBlk>(count, &tot);
-    if (threadIdx.x == 0) w.blk_sum[blockIdx.x] = tot;
+    unsigned long long slots = 0ull;
+    for (int i = 0; i < bs.iters; ++i) {
+        const int g = share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
+        const size_t vg = (size_t)v * rp.M + g;
+        unsigned int n = 0u, t0 = 0u, span = 0u, kept = 0u;
+        ProjOut p;
+        if (g < rp.M) {
+            p = project_one<SH>(V, rp, gp, g);
+            TileRect r;
+            if (p.valid && rect_of(p.r0.x, p.r0.y, p.r2.z, p.r2.w, V.cam.W, V.cam.H, rp.tile_w, rp.tile_h, &r)) {
+                const unsigned int width = (unsigned int)(r.tx1 - r.tx0 + 1), height = (unsigned int)(r.ty1 - r.ty0 + 1);
+                n = width * height;  // one slot per covered tile
+                span = width | height << 16;
+                t0 = (unsigned int)r.tx0 | (unsigned int)r.ty0 << 16;
+                w.rec[3 * vg + 0] = p.r0;
+                w.rec[3 * vg + 1] = p.r1;
+                w.rec[3 * vg + 2] = p.r2;
+                w.off[vg] = t0;
+                w.depth[vg] = p.r1.z;
+            }
+            w.span[vg] = span;
+        }
+        const unsigned int excl = wave_incl_sum(n) - n;
+        const unsigned int total = (unsigned int)__builtin_amdgcn_readlane((int)(excl + n), 63);
+        slots += total;
+        if (slots > rp.cap) continue;  // over the capacity: nothing of this forward is used
+        const unsigned long long seen = __builtin_amdgcn_ballot_w64(n > 0u);
+        const unsigned int at = lanes_before(seen);
+        wave_lds_order();
+        if (n > 0u) {
+            const SupportTest st(p.r0, p.r1, l2amin);  // made once for all slots
+            ww.a[at] = make_float4(st.mx, st.my, st.A, st.B);
+            ww.b[at] = make_float4(st.C, st.kx, st.ky, st.need);
+            ww.c[at] = make_uint4(__float_as_uint(p.r1.z), excl, t0, span & 0xffffu);
+        }
+        unsigned int before = 0u;
+        for (unsigned int w0 = 0u; w0 < total; w0 += 64u) {
+            const unsigned int owner = walk_owner(ww, n, excl, w0, before);
+            bool pass = false;
+            if (w0 + lane < total) {
+                const uint4 c = ww.c[owner];
+                int tx, ty;
+                const Slot s = slot_of<LDS>(c, w0 + lane, V.tiles_x, &tx, &ty);
+                const float tile_max = w.tilemax[V.tile_base + s.tile];
+                pass = slot_passes(SupportTest(ww.a[owner], ww.b[owner]), __uint_as_float(c.x), tx, ty, tile_max, rp);
+                if (pass) atomicAdd(LDS ? &counter[s.tile] : row + s.tile, 1u);
+            }
+            // this lane's Gaussian takes the bits of its slots in the window
+            const unsigned long long passed = __builtin_amdgcn_ballot_w64(pass);
+            const unsigned int all = 0xffffffffu >> (kKeptBits - min(n, (unsigned int)kKeptBits) & 31u);
+            const int lo = (int)(excl - w0);
+            if (lo >= 0 && lo < 64) kept |= (unsigned int)(passed >> lo) & all;
+            else if (lo < 0 && lo > -kKeptBits) kept |= (unsigned int)(passed << -lo) & all;
+        }
+        if (n > 0u) w.kept[vg] = kept;
+    }
+    if (lane == 0) w.seg_sum[blockIdx.x * WAVES + wid] = (unsigned int)min(slots, 0xffffffffull);
+    if (LDS) {
+        __syncthreads();
+        for (int t = threadIdx.x; t < n_tiles; t += 64 * WAVES) row[t] = counter[t];
+    }
+}
+
+// The shared rows of tile counts start at zero.
+__global__ void __launch_bounds__(kBlk) k_zero_rows(WsPtrs w, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * kBlk + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlk) w.tile_rows[i] = 0u;
 }
 
 // ------------------------------------------------------------------- scan
-// One block of 1024 lanes: exclusive scan of the per-block instance counts and
-// of the per-tile counts; capacity check.
-__device__ unsigned long long scan_array_1024(const unsigned int* in, unsigned int* out, int n, int write_total)
+// Per tile: the rows of counts become the first place of each row inside the tile's range,
+// and the tile's instances their sum.  kScanCols tiles per block, the rows in as many
+// groups of consecutive ones as lanes are left; a lane has its rows in flight together.
+constexpr int kScanCols = 16, kScanGroups = kBlk / kScanCols, kScanRows = 32;
+
+// The slots of the projection's wavefronts: their first, and the total against the capacity.
+// One block.  The total may pass 32 bits (it is then over the capacity and no place is used).
+__device__ void scan_segments(const RParams& rp, const BinShape& bs, const WsPtrs& w, int n_tiles)
 {
-    __shared__ unsigned int wsum[16];
-    __shared__ unsigned long long carry_s;
-    if (threadIdx.x == 0) carry_s = 0ull;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int base = 0; base < n; base += 4096) {
-        unsigned int v[4], sum = 0;
+    constexpr int kPer = 16;
+    __shared__ unsigned long long wsum[kBlk / 64];
+    const int n = rp.V * bs.chunks * bs.waves, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    unsigned long long carry = 0ull;
+    for (int base = 0; base < n; base += kBlk * kPer) {
+        struct alignas(16) Segs {
+            unsigned int n[kPer];
+        } cv{};
+        unsigned int (&c)[kPer] = cv.n;
+        unsigned long long sum = 0ull;
+        const int t0 = base + threadIdx.x * kPer;
+        if (t0 < n) cv = *reinterpret_cast<const Segs*>(w.seg_sum + t0);  // (the array is longer than kMostSegs rounded up)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int i = base + threadIdx.x * 4 + k;
-            v[k] = i < n ? in[i] : 0u;
-            sum += v[k];
-        }
-        unsigned int x = sum;
+        for (int i = 0; i < kPer; ++i) c[i] = t0 + i < n ? c[i] : 0u;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) sum += c[i];
+        unsigned long long x = sum;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
-            unsigned int y = __shfl_up(x, o, 64);
+            const unsigned long long y = __shfl_up(x, o, 64);
             if (lane >= o) x += y;
         }
         if (lane == 63) wsum[wid] = x;
         __syncthreads();
-        unsigned int before = 0, tot = 0;
-        for (int k = 0; k < 16; ++k) {
-            if (k < wid) before += wsum[k];
-            tot += wsum[k];
-        }
-        unsigned long long carry = carry_s;
-        unsigned int run = (unsigned int)carry + before + x - sum;
+        unsigned long long before = carry;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int i = base + threadIdx.x * 4 + k;
-            if (i < n) out[i] = run;
-            run += v[k];
+        for (int k = 0; k < kBlk / 64; ++k) {
+            if (k < wid) before += wsum[k];
+            carry += wsum[k];
         }
-        __syncthreads();
-        if (threadIdx.x == 0) carry_s = carry + tot;
+        unsigned int run = (unsigned int)(before + x - sum);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const unsigned int s = c[i];
+            c[i] = run;
+            run += s;
+        }
+        if (t0 < n) *reinterpret_cast<Segs*>(w.seg_off + t0) = cv;
         __syncthreads();
     }
-    unsigned long long total = carry_s;
-    if (write_total && threadIdx.x == 0) out[n] = (unsigned int)total;
-    __syncthreads();
-    return total;
-}
-
-__global__ void __launch_bounds__(1024) k_scan_blocks(const ViewTable* __restrict__ vtp, RParams rp, WsPtrs w,
-                                                     int nblk_vg, int n_tiles, int resets)
-{
-    if (resets) forward_resets(*vtp, rp, w);  // no projection launch (no Gaussians): the resets are here
-    unsigned long long total = scan_array_1024(w.blk_sum, w.blk_off, nblk_vg, 0);
     if (threadIdx.x == 0) {
-        w.hdr->n_inst = total;
+        w.hdr->n_inst = carry;
         w.hdr->cap = rp.cap;
         w.hdr->n_tiles = n_tiles;
-        if (total > rp.cap) atomicCAS(&w.hdr->status, 0, GPS_ERR_CAPACITY);
+        w.hdr->n_views = rp.V;
+        w.hdr->n_fallback = 0ull;
+        if (carry > rp.cap) atomicCAS(&w.hdr->status, 0, GPS_ERR_CAPACITY);
     }
 }
 
-// Also orders the tiles for the compositing kernels, longest first:
-// tiles are bucketed by floor(log2(count + 1)) and the buckets laid out in
-// descending order.  The order inside a bucket is arbitrary; it affects only
-// which block processes a tile, never a result.
+// Block 0 scans the segments, the others the rows of kScanCols tiles each.
+__global__ void __launch_bounds__(kBlk) k_scan_rows(const ViewTable* __restrict__ vtp, RParams rp, BinShape bs, WsPtrs w)
+{
+    const ViewTable& vt = *vtp;
+    if (blockIdx.x == 0) {
+        scan_segments(rp, bs, w, vt.n_tiles);
+        return;
+    }
+    __shared__ unsigned int sum[kScanGroups][kScanCols + 1];
+    const int col = threadIdx.x % kScanCols, grp = threadIdx.x / kScanCols;
+    const int tile = (blockIdx.x - 1) * kScanCols + col;
+    const bool live = tile < vt.n_tiles;
+    const int v = find_view(vt, live ? tile : 0);
+    const DevView& V = vt.v[v];
+    const size_t n_tiles = (size_t)V.tiles_x * V.tiles_y;
+    unsigned int* p = w.tile_rows + (size_t)bs.rows * V.tile_base + (live ? tile - V.tile_base : 0);
+    const int per = (bs.rows + kScanGroups - 1) / kScanGroups;
+    const int r0 = min(grp * per, bs.rows), r1 = live ? min(r0 + per, bs.rows) : r0;
+    unsigned int c[kScanRows], s = 0u;
+    for (int r = r0; r < r1; r += kScanRows) {
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) c[k] = r + k < r1 ? p[(size_t)(r + k) * n_tiles] : 0u;
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) s += c[k];
+    }
+    sum[grp][col] = s;
+    __syncthreads();
+    unsigned int run = 0u;
+    for (int k = 0; k < grp; ++k) run += sum[k][col];
+    if (live && grp == kScanGroups - 1) w.tile_cnt[tile] = run + s;
+    for (int r = r0; r < r1; r += kScanRows) {
+        if (per > kScanRows) {  // not all in registers
+#pragma unroll
+            for (int k = 0; k < kScanRows; ++k) c[k] = r + k < r1 ? p[(size_t)(r + k) * n_tiles] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kScanRows; ++k) {
+            if (r + k < r1) p[(size_t)(r + k) * n_tiles] = run;
+            run += c[k];
+        }
+    }
+}
+
+// Position of this lane in its bucket's list: the lanes of one bucket go to the next places of
+// cur[bucket] together (one LDS atomic per bucket and wavefront: with one per lane,
+// a few buckets hold all tiles and the atomics queue).  Returns the place.
+__device__ __forceinline__ unsigned int bucket_add(unsigned int* cur, bool has, int bucket)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned int place = 0u;
+    unsigned long long left = __builtin_amdgcn_ballot_w64(has);
+    while (left) {
+        const int lead = (int)__builtin_ctzll(left);
+        const int b = __builtin_amdgcn_readlane(bucket, lead);
+        const unsigned long long same = __builtin_amdgcn_ballot_w64(has && bucket == b);
+        unsigned int base = 0u;
+        if (lane == lead) base = atomicAdd(&cur[b], (unsigned int)__builtin_popcountll(same));
+        base = (unsigned int)__builtin_amdgcn_readlane((int)base, lead);
+        if (has && bucket == b) place = base + lanes_before(same);
+        left &= ~same;
+    }
+    return place;
+}
+
+// One block: the tile ranges, and the tiles in order for the compositing kernels, longest
+// first: tiles are bucketed by floor(log2(count + 1)) and the buckets laid out in descending
+// order.  The order inside a bucket is arbitrary; it affects only which block processes a
+// tile, never a result.  A lane has PER consecutive tiles; with more than 1024 PER tiles the
+// block takes them in passes and leaves a tile's place in its bucket in tile_cnt between.
+constexpr int kLongBucket = 9;
+static_assert(kLongTile == (1u << kLongBucket) - 1u, "the long tiles are whole buckets");
+
+template <int PER>
 __global__ void __launch_bounds__(1024) k_scan_tiles(RParams rp, WsPtrs w, int n_tiles)
 {
-    if (w.hdr->n_inst > rp.cap) return;
-    __shared__ unsigned int wsum[16], hist[33], cur[33];
-    __shared__ unsigned int carry_s, n_large;
-    if (threadIdx.x < 33) hist[threadIdx.x] = 0u;
-    if (threadIdx.x == 0) {
-        carry_s = 0u;
-        n_large = 0u;
-    }
-    __syncthreads();
+    __shared__ unsigned int wsum[16], hist[33];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    unsigned int last_tot[4] = {0u, 0u, 0u, 0u};  // the lane's tile lengths in the last chunk
-    // One pass per chunk of 4 tiles per lane: the sub-counts are read once, their
-    // totals scanned over the block (chunks carried in order) into the tile
-    // ranges, each sub-counter replaced by the start of its range inside its
-    // tile's range, and the tile lengths counted into the histogram.
-    for (int base = 0; base < n_tiles; base += 4 * 1024) {
-        unsigned int c[4][kCntSplit], tot[4], sum = 0u;
+    // A lane's tiles are one aligned vector (the arrays are padded to 256 bytes): on one CU the
+    // accesses count, and eight of 4 bytes a lane took 18 us over 7360 tiles, this 12.
+    struct alignas(PER >= 4 ? 16 : 4 * PER) Tiles {
+        unsigned int n[PER];
+    };
+    Tiles* const cnt = reinterpret_cast<Tiles*>(w.tile_cnt);
+    Tiles* const start = reinterpret_cast<Tiles*>(w.tile_start);
+    Tiles c, place, begin;
+    auto load = [&](int t0) {
+        if (t0 < n_tiles) c = cnt[t0 / PER];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = base + threadIdx.x * 4 + i;
-            tot[i] = 0u;
+        for (int i = 0; i < PER; ++i) c.n[i] = t0 + i < n_tiles ? c.n[i] : 0u;
+    };
+    const unsigned long long n_inst = w.hdr->n_inst;
+    load(threadIdx.x * PER);
+    if (threadIdx.x < 33) hist[threadIdx.x] = 0u;
+    if (n_inst > rp.cap) return;  // below, every sum fits 32 bits
+    const bool passes = n_tiles > 1024 * PER;
+    unsigned int carry = 0u;
+    for (int base = 0; base < n_tiles; base += 1024 * PER) {
+        const int t0 = base + threadIdx.x * PER;
+        unsigned int s = 0u;
+        if (base > 0) load(t0);
 #pragma unroll
-            for (int k = 0; k < kCntSplit; ++k) {
-                c[i][k] = t < n_tiles ? w.tile_cnt[(size_t)k * n_tiles + t] : 0u;
-                tot[i] += c[i][k];
-            }
-            sum += tot[i];
-        }
-        unsigned int x = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned int y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
+        for (int i = 0; i < PER; ++i) s += c.n[i];
+        const unsigned int x = wave_incl_sum(s);
+        __syncthreads();  // hist and wsum are free
         if (lane == 63) wsum[wid] = x;
-        __syncthreads();
-        unsigned int before = 0u, total = 0u;
-        for (int k = 0; k < 16; ++k) {
-            if (k < wid) before += wsum[k];
-            total += wsum[k];
-        }
-        const unsigned int carry = carry_s;
-        unsigned int run = carry + before + x - sum;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = base + threadIdx.x * 4 + i;
-            if (t < n_tiles) {
-                w.tile_start[t] = run;
-                unsigned int r = run;
+        for (int i = 0; i < PER; ++i) place.n[i] = bucket_add(hist, t0 + i < n_tiles, 31 - __clz(c.n[i] + 1u));
+        __syncthreads();
+        const unsigned int ws = lane < 16 ? wsum[lane] : 0u;
+        const unsigned int wx = wave_incl_sum(ws);  // lane k: sum over wavefronts 0 .. k
+        const unsigned int before = wid == 0 ? 0u : (unsigned int)__builtin_amdgcn_readlane((int)wx, wid - 1);
+        unsigned int run = carry + before + x - s;
 #pragma unroll
-                for (int k = 0; k < kCntSplit; ++k) {
-                    w.tile_cnt[(size_t)k * n_tiles + t] = r;
-                    r += c[i][k];
-                }
-                atomicAdd(&hist[31 - __clz(tot[i] + 1u)], 1u);
-                if (tot[i] >= kLongTile) atomicAdd(&n_large, 1u);
-            }
-            last_tot[i] = tot[i];
-            run += tot[i];
+        for (int i = 0; i < PER; ++i) {
+            begin.n[i] = run;
+            run += c.n[i];
         }
-        __syncthreads();
-        if (threadIdx.x == 0) carry_s = carry + total;
-        __syncthreads();
+        if (t0 < n_tiles) {
+            start[t0 / PER] = begin;  // (the entry behind the last tile is the end of its range)
+            if (passes) cnt[t0 / PER] = place;
+        }
+        carry += (unsigned int)__builtin_amdgcn_readlane((int)wx, 15);
     }
-    // Longest-first order: buckets floor(log2(count + 1)) laid out in descending order.
+    // bucket b starts after all longer ones: lane k has the start of bucket 32 - k
+    const unsigned int h = lane < 33 ? hist[32 - lane] : 0u;
+    const unsigned int first = wave_incl_sum(h) - h;
+    const int n_long = __builtin_amdgcn_readlane((int)first, 32 - (kLongBucket - 1));
     if (threadIdx.x == 0) {
-        w.tile_start[n_tiles] = carry_s;
-        w.hdr->n_large = n_large;
-        unsigned int o = 0;
-        for (int bkt = 32; bkt >= 0; --bkt) {
-            cur[bkt] = o;
-            o += hist[bkt];
-        }
+        w.tile_start[n_tiles] = carry;
+        w.hdr->n_large = (unsigned int)n_long;
     }
-    __syncthreads();
-    if (n_tiles <= 4 * 1024) {
-        // one chunk: this lane's four tile lengths are still in registers
+    if (!passes) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = threadIdx.x * 4 + i;
-            if (t < n_tiles) w.tile_queue[atomicAdd(&cur[31 - __clz(last_tot[i] + 1u)], 1u)] = (unsigned int)t;
+        for (int i = 0; i < PER; ++i) {
+            const int t = threadIdx.x * PER + i;
+            const unsigned int st = (unsigned int)__shfl((int)first, 32 - (31 - __clz(c.n[i] + 1u)), 64);
+            if (t < n_tiles) w.tile_queue[st + place.n[i]] = (unsigned int)t;
         }
         return;
     }
-    for (int i = threadIdx.x; i < n_tiles; i += 1024) {
-        const unsigned int pos = atomicAdd(&cur[31 - __clz(w.tile_start[i + 1] - w.tile_start[i] + 1u)], 1u);
-        w.tile_queue[pos] = (unsigned int)i;
+    __syncthreads();  // tile_start and tile_cnt of the block's lanes
+    for (int base = 0; base < n_tiles; base += 1024) {
+        const int t = base + threadIdx.x;
+        const unsigned int n = t < n_tiles ? w.tile_start[t + 1] - w.tile_start[t] : 0u;
+        const unsigned int st = (unsigned int)__shfl((int)first, 32 - (31 - __clz(n + 1u)), 64);
+        if (t < n_tiles) w.tile_queue[st + w.tile_cnt[t]] = (unsigned int)t;
     }
 }
 
-// ------------------------------------------------------------ count / emit
-// Block-cooperative expansion of the instances of kExpG consecutive
-// view-Gaussians (a share of one projection block of kBlk): the block's kBlk
-// lanes walk the concatenation of their tile rectangles together (instance i
-// belongs to the Gaussian whose prefix range holds i, found by binary search in
-// LDS), so one large Gaussian, or a run of dense ones, is spread over several
-// lanes per Gaussian instead of serialising one lane.  Slots are numbered per
-// projection block: instance i of projection block b has slot blk_off[b] + i,
-// whichever expansion block handles it.
-//   COUNT:  tiles that the support ellipse meets (SupportTest) and that pass
-//           the exact depth cull get one of their kCntSplit sub-counters
-//           (chosen by block index) incremented; the count before the increment
-//           (the instance's rank in that sub-counter) is parked in inst_vg[slot];
-//           the per-view-Gaussian slot offsets are written.
-//   EMIT:   the same instances (the culls are the same binary32 tests on the
-//           same values, the block index the same) write the key
-//           (depth bits << 32) | view-Gaussian at the sub-counter's start + rank,
-//           with no atomics, and zero the instance partials of every slot.  A
-//           tile holds at most one instance of a view-Gaussian, and slots grow
-//           with the view-Gaussian index, so the keys sort as (depth, slot) would;
-//           the backward recovers the slot from the view-Gaussian's offset and the
-//           tile's place in its rectangle.
-template <bool EMIT>
-__global__ void __launch_bounds__(kBlk) k_expand(const ViewTable* __restrict__ vtp, RParams rp, WsPtrs w)
+// ------------------------------------------------------------------- emit
+// The same walk: every instance that passed writes the key (depth bits << 32) |
+// view-Gaussian at the next place of its tile in its block's part of the range, and the
+// view-Gaussian its first slot.  A tile holds at most one instance of a view-Gaussian, and
+// slots grow with the view-Gaussian index inside a wavefront's share, so the keys' order does
+// not depend on places; the backward finds the slot from the view-Gaussian's first and the
+// tile's place in its rectangle.  The backward reads the slots of a Gaussian by its bits; one
+// with more slots than bits is tested again here and the partials of its
+// other slots zeroed.  Bound by the scattered 8-byte stores for many instances (8.5 M: 126 us; with every
+// slot's partial zeroed and the culls repeated 275).
+template <int WAVES, int PER, bool LDS>
+__global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restrict__ vtp, RParams rp, BinShape bs, WsPtrs w)
 {
-    constexpr int kSplit = kBlk / kExpG;  // expansion blocks per projection block
+    extern __shared__ unsigned int counter[];  // LDS: next place per tile of the view
+    __shared__ EmitWalk<PER> walk[WAVES];
     const ViewTable& vt = *vtp;
-    __shared__ unsigned int pre[kExpG + 1];
-    __shared__ float4 sbox[kExpG];  // mx, my, rxp, ryp
-    __shared__ float4 scon[kExpG];  // the exponent's coefficients A, B, C and log2 sigma
-    __shared__ float sz[kExpG];
-    __shared__ int4 sview[kExpG];   // tile_base, tiles_x, W, H
-    const int pb = blockIdx.x / kSplit;
-    const int g0 = (blockIdx.x % kSplit) * kExpG;  // first lane (Gaussian) of this block's share
-    const int vg = pb * kBlk + threadIdx.x;         // lane k: Gaussian k of the projection block
-    const int k = threadIdx.x - g0;
-    // The count, the record of this block's share (written by the projection for every
-    // view-Gaussian) and the block's slot base are loaded together with the capacity
-    // check, before any of them is waited for.
-    const bool mine = k >= 0 && k < kExpG && vg < rp.nvg;
-    const unsigned long long n_inst = w.hdr->n_inst;
-    const unsigned int c = vg < rp.nvg ? w.cnt[vg] : 0u;
-    float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
-    if (mine) {
-        r0 = w.rec[3 * (size_t)vg];
-        r1 = w.rec[3 * (size_t)vg + 1];
-        r2 = w.rec[3 * (size_t)vg + 2];
-    }
-    const unsigned int base = w.blk_off[pb];
-    if (n_inst > rp.cap) return;
-    unsigned int tot;
-    const unsigned int excl = block_excl_scan<kBlk>(c, &tot);  // prefix within the projection block
-    if (k >= 0 && k < kExpG) {
-        pre[k] = excl;
-        if (k == kExpG - 1) pre[kExpG] = excl + c;
-        if (c > 0) {
-            sbox[k] = make_float4(r0.x, r0.y, r2.z, r2.w);
-            scon[k] = make_float4(r0.z, r0.w, r1.x, r1.y);
-            sz[k] = r1.z;
-            const DevView& V = vt.v[vg / rp.M];
-            sview[k] = make_int4(V.tile_base, V.tiles_x, V.cam.W, V.cam.H);
+    const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
+    const DevView& V = vt.v[v];
+    const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
+    const unsigned int* start = w.tile_start + V.tile_base;
+    EmitWalk<PER>& ww = walk[wid];
+    // A Gaussian's loads are issued an iteration ahead.
+    unsigned int span = 0u, t0 = 0u, kept = 0u, span1 = 0u, t01 = 0u, kept1 = 0u;
+    float z = 0.0f, z1 = 0.0f;
+    auto load = [&](int i) {
+        const int g = i < bs.iters ? share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M) : rp.M;
+        span1 = 0u;
+        if (g < rp.M) {
+            const size_t vg = (size_t)v * rp.M + g;
+            span1 = w.span[vg];
+            t01 = w.off[vg];
+            kept1 = w.kept[vg];
+            z1 = w.depth[vg];
         }
-        if (!EMIT && vg < rp.nvg) w.off[vg] = base + excl;
+    };
+    load(0);
+    unsigned int base = w.seg_off[blockIdx.x * WAVES + wid];
+    if (w.hdr->n_inst > rp.cap) return;
+    if (LDS) {
+        for (int t = threadIdx.x; t < n_tiles; t += 64 * WAVES) counter[t] = start[t] + row[t];
+        __syncthreads();
     }
-    // sub-counter of this block: the same block index, so the same sub-counter, in both passes
-    const size_t sub = (size_t)(blockIdx.x % kCntSplit) * vt.n_tiles;
-    __syncthreads();
-    const unsigned int first = pre[0], last = pre[kExpG];
     const float l2amin = __log2f(rp.amin);
-    for (unsigned int i = first + threadIdx.x; i < last; i += kBlk) {
-        int lo = 0, hi = kExpG;  // pre[lo] <= i < pre[hi]
+    for (int i = 0; i < bs.iters; ++i) {
+        const size_t vg = (size_t)v * rp.M + share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
+        span = span1;
+        t0 = t01;
+        kept = kept1;
+        z = z1;
+        load(i + 1);
+        const unsigned int n = (span & 0xffffu) * (span >> 16);
+        const unsigned int excl = wave_incl_sum(n) - n;
+        const unsigned int total = (unsigned int)__builtin_amdgcn_readlane((int)(excl + n), 63);
+        const unsigned long long seen = __builtin_amdgcn_ballot_w64(n > 0u);
+        const unsigned int at = lanes_before(seen);
+        const bool big = n > (unsigned int)kKeptBits;
+        wave_lds_order();
+        if (n > 0u) {
+            w.off[vg] = base + excl;
+            ww.c[at] = make_uint4(__float_as_uint(z), excl, t0, (span & 0xffffu) | (unsigned int)lane << 16 | (big ? 0x80000000u : 0u));
+            ww.kept[at] = kept;
+        }
+        unsigned int before = 0u;
+        for (unsigned int w0 = 0u; w0 < total; w0 += 64u) {
+            const unsigned int owner = walk_owner(ww, n, excl, w0, before);
+            if (w0 + lane < total) {
+                const uint4 c = ww.c[owner];
+                int tx, ty;
+                const Slot s = slot_of<LDS>(c, w0 + lane, V.tiles_x, &tx, &ty);
+                const int owner_g = share_gaussian<PER>(bs, chunk, wid, (c.w >> 16) & 63, i, rp.M);
+                bool pass;
+                if (s.small) {
+                    pass = (ww.kept[owner] >> s.j) & 1u;
+                } else {
+                    const float4* r = w.rec + 3 * ((size_t)v * rp.M + owner_g);
+                    pass = slot_passes(SupportTest(r[0], r[1], l2amin), __uint_as_float(c.x), tx, ty,
+                                       w.tilemax[V.tile_base + s.tile], rp);
+                    if (!pass) {
+                        float* pz = w.partial + (size_t)(base + w0 + lane) * kAdj;
 #pragma unroll
-        for (int step = 0; step < kExpGLog2; ++step) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= i) lo = mid;
-            else hi = mid;
+                        for (int q = 0; q < kAdj; ++q) pz[q] = 0.0f;
+                    }
+                }
+                if (pass) {
+                    const unsigned int pos = LDS ? atomicAdd(&counter[s.tile], 1u) : start[s.tile] + atomicAdd(row + s.tile, 1u);
+                    // key: depth bits, then the view-Gaussian
+                    if (pos < rp.cap)
+                        w.keys[pos] = ((unsigned long long)c.x << 32) | (unsigned int)(v * rp.M + owner_g);
+                }
+            }
         }
-        const unsigned int j = i - pre[lo];
-        const float4 bx = sbox[lo];
-        const int4 vw = sview[lo];
-        TileRect r;
-        if (!rect_of(bx.x, bx.y, bx.z, bx.w, vw.z, vw.w, rp.tile_w, rp.tile_h, &r)) continue;
-        const unsigned int wdt = (unsigned int)(r.tx1 - r.tx0 + 1);
-        const int tix = r.tx0 + (int)(j % wdt), tiy = r.ty0 + (int)(j / wdt);
-        const int tile = vw.x + tiy * vw.y + tix;
-        const float z = sz[lo];
-        const unsigned int slot = base + i;
-        if (EMIT) {
-            // The per-Gaussian reduce sums every slot of a Gaussian: all slots start at
-            // zero (culled ones, and those the backward's tiles stop before, stay so).
-            float* pz = w.partial + (size_t)slot * kAdj;
-#pragma unroll
-            for (int q = 0; q < kAdj; ++q) pz[q] = 0.0f;
-        }
-        // the support ellipse must meet the tile (its box may only overlap it)
-        const float4 cn = scon[lo];
-        const SupportTest st(make_float4(bx.x, bx.y, cn.x, cn.y), make_float4(cn.z, cn.w, 0.0f, 0.0f), l2amin);
-        if (!st.meets((float)(tix * rp.tile_w), (float)(tiy * rp.tile_h), (float)rp.tile_w, (float)rp.tile_h)) continue;
-        if (!(z < w.tilemax[tile] + rp.eps)) continue;  // exact tile-level depth cull
-        if (!EMIT) {
-            w.inst_vg[slot] = atomicAdd(w.tile_cnt + sub + tile, 1u);
-        } else {
-            // key: depth bits, then the view-Gaussian (within a tile it orders as the slot does)
-            const unsigned int pos = w.tile_cnt[sub + tile] + w.inst_vg[slot];
-            if (pos < w.tile_start[tile + 1])
-                w.keys[pos] = ((unsigned long long)__float_as_uint(z) << 32) | (unsigned int)(pb * kBlk + g0 + lo);
-        }
+        base += total;
     }
 }
 
@@ -883,6 +1097,26 @@ gps_status launch_views_upload(const ViewTable& vt, const RParams& rp, const WsL
 }
 
 // ----------------------------------------------------------------- launch
+template <int WAVES, int PER>
+static void launch_project(const ViewTable* vt, const RParams& rp, const BinShape& bs, const GParams& gp, const WsPtrs& w,
+                           hipStream_t s)
+{
+    const dim3 grid((unsigned int)(bs.chunks * rp.V)), blk(64 * WAVES);
+    const size_t lds = 4 * (size_t)bs.lds_words;
+    if (bs.lds && gp.sh_k) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, true, true>), grid, blk, lds, s, vt, rp, bs, gp, w);
+    else if (bs.lds) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, true, false>), grid, blk, lds, s, vt, rp, bs, gp, w);
+    else if (gp.sh_k) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, false, true>), grid, blk, 0, s, vt, rp, bs, gp, w);
+    else GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, false, false>), grid, blk, 0, s, vt, rp, bs, gp, w);
+}
+
+template <int WAVES, int PER>
+static void launch_emit(const ViewTable* vt, const RParams& rp, const BinShape& bs, const WsPtrs& w, hipStream_t s)
+{
+    const dim3 grid((unsigned int)(bs.chunks * rp.V)), blk(64 * WAVES);
+    if (bs.lds) GPS_LAUNCH(K_EMIT, s, (k_emit<WAVES, PER, true>), grid, blk, 4 * (size_t)bs.lds_words, s, vt, rp, bs, w);
+    else GPS_LAUNCH(K_EMIT, s, (k_emit<WAVES, PER, false>), grid, blk, 0, s, vt, rp, bs, w);
+}
+
 gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const gps_gaussians* g,
                              const ViewTable& vt, const WsLayout& L, char* ws, float* out_loss, hipStream_t s)
 {
@@ -898,14 +1132,23 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
         const gps_status st = launch_views_upload(vt, rp, L, ws, 1, s);
         if (st != GPS_OK) return st;
     }
-    if (L.nblk_vg > 0) GPS_LAUNCH(K_PROJECT, s, k_project, dim3(L.nblk_vg), dim3(kBlk), 0, s, dvt, rp, gp, w);
-    GPS_LAUNCH(K_SCAN, s, k_scan_blocks, dim3(1), dim3(1024), 0, s, dvt, rp, w, L.nblk_vg, L.n_tiles,
-               L.nblk_vg > 0 ? 0 : 1);
-    if (L.nblk_vg > 0)
-        GPS_LAUNCH(K_TILE_COUNT, s, k_expand<false>, dim3(L.nblk_vg * (kBlk / kExpG)), dim3(kBlk), 0, s, dvt, rp, w);
-    GPS_LAUNCH(K_SCAN_TILES, s, k_scan_tiles, dim3(1), dim3(1024), 0, s, rp, w, L.n_tiles);
-    if (L.nblk_vg > 0)
-        GPS_LAUNCH(K_EMIT, s, k_expand<true>, dim3(L.nblk_vg * (kBlk / kExpG)), dim3(kBlk), 0, s, dvt, rp, w);
+    const BinShape& bs = L.bin;
+    if (bs.chunks > 0) {
+        if (!bs.lds) {
+            const size_t n = (size_t)bs.rows * L.n_tiles;
+            GPS_LAUNCH(K_SCAN, s, k_zero_rows, dim3((unsigned int)std::min((n + kBlk - 1) / kBlk, (size_t)1024)),
+                       dim3(kBlk), 0, s, w, n);
+        }
+        if (bs.per == kFewPer) launch_project<kFewWaves, kFewPer>(dvt, rp, bs, gp, w, s);
+        else launch_project<kManyWaves, kManyPer>(dvt, rp, bs, gp, w, s);
+    }
+    GPS_LAUNCH(K_SCAN, s, k_scan_rows, dim3(1 + (L.n_tiles + kScanCols - 1) / kScanCols), dim3(kBlk), 0, s, dvt, rp, bs, w);
+    if (L.n_tiles <= 2048) GPS_LAUNCH(K_SCAN_TILES, s, k_scan_tiles<2>, dim3(1), dim3(1024), 0, s, rp, w, L.n_tiles);
+    else GPS_LAUNCH(K_SCAN_TILES, s, k_scan_tiles<8>, dim3(1), dim3(1024), 0, s, rp, w, L.n_tiles);
+    if (bs.chunks > 0) {
+        if (bs.per == kFewPer) launch_emit<kFewWaves, kFewPer>(dvt, rp, bs, w, s);
+        else launch_emit<kManyWaves, kManyPer>(dvt, rp, bs, w, s);
+    }
     if (rp.mode != 2)  // the unsorted sort-free blend keeps the emission order
         GPS_LAUNCH(K_TILE_SORT_LARGE, s, k_tile_sort_large, dim3(L.n_tiles < kSortGrid ? L.n_tiles : kSortGrid),
                    dim3(kSortThreads), 0, s, rp, w);
