@@ -36,6 +36,9 @@ class Camera(ctypes.Structure):
                 ("R", ctypes.c_float * 9), ("t", ctypes.c_float * 3)]
 
 
+_F9, _F3 = ctypes.c_float * 9, ctypes.c_float * 3
+
+
 class VolumeS(ctypes.Structure):
     _fields_ = [("nx", ctypes.c_int32), ("ny", ctypes.c_int32), ("nz", ctypes.c_int32),
                 ("origin", ctypes.c_float * 3), ("voxel", ctypes.c_float), ("trunc", ctypes.c_float),
@@ -183,23 +186,25 @@ def _check(st: int, what: str):
 def _stream(stream=None):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _ptr(t, name="tensor", numel=None):
+    """The device address of a tensor the library may read or write (an int: ctypes takes it for a
+    pointer argument, field or array element without a c_void_p object in between), or None."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
-    if t.dtype not in (torch.float32, torch.int32, torch.int64, torch.uint8):
+    if t.dtype is not torch.float32 and t.dtype not in (torch.int32, torch.int64, torch.uint8):
         raise TypeError(f"{name} must be float32 (got {t.dtype})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if numel is not None and t.numel() != numel:
         raise ValueError(f"{name} has {t.numel()} elements, expected {numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # --------------------------------------------------------------------------- #
@@ -210,16 +215,10 @@ def camera(c) -> Camera:
     if isinstance(c, Camera):
         return c
     g = (lambda k: c[k]) if isinstance(c, dict) else (lambda k: getattr(c, k))
-    out = Camera()
-    out.width, out.height = int(g("width")), int(g("height"))
-    out.fx, out.fy, out.cx, out.cy = (float(g(k)) for k in ("fx", "fy", "cx", "cy"))
     R = np.asarray(g("R"), np.float32).reshape(9)
     t = np.asarray(g("t"), np.float32).reshape(3)
-    for k in range(9):
-        out.R[k] = float(R[k])
-    for k in range(3):
-        out.t[k] = float(t[k])
-    return out
+    return Camera(int(g("width")), int(g("height")), float(g("fx")), float(g("fy")), float(g("cx")), float(g("cy")),
+                  _F9(*R.tolist()), _F3(*t.tolist()))
 
 
 @dataclass
@@ -290,14 +289,9 @@ def sh_degree(g: dict) -> int:
 
 def gaussians_struct(g: dict) -> GaussiansS:
     M = int(g["opacity_logit"].numel())
-    s = GaussiansS()
-    s.count = M
-    for k in GAUSS_KEYS:
-        setattr(s, k, _ptr(g[k], k, GAUSS_ROWS[k] * M))
+    five = [_ptr(g[k], k, GAUSS_ROWS[k] * M) for k in GAUSS_KEYS]
     L = sh_degree(g)
-    s.sh_degree = L
-    s.sh = _ptr(g["sh"], "sh", 3 * SH_COEFFS[L] * M) if L > 0 else None
-    return s
+    return GaussiansS(M, *five, L, _ptr(g["sh"], "sh", 3 * SH_COEFFS[L] * M) if L > 0 else None)
 
 
 def gaussians_to_device(g: dict, device="cuda") -> dict:
@@ -307,6 +301,11 @@ def gaussians_to_device(g: dict, device="cuda") -> dict:
 
 def zeros_like_gaussians(g: dict) -> dict:
     return {k: torch.zeros_like(g[k]) for k in gauss_keys(g)}
+
+
+def _empty_like_gaussians(g: dict) -> dict:
+    """Gradients for render_bwd, which writes every element (zeros after a capacity overflow too)."""
+    return {k: torch.empty_like(g[k]) for k in gauss_keys(g)}
 
 
 @dataclass
@@ -361,8 +360,8 @@ def raycast(vol: Volume, cams, z_near=0.2, step=0.0, out=None, stream=None):
         out = [(torch.empty(c.height, c.width, dtype=torch.float32, device=vol.tsdf.device),
                 torch.empty(3, c.height, c.width, dtype=torch.float32, device=vol.tsdf.device)) for c in cams]
     carr = (Camera * V)(*cams)
-    dptr = (ctypes.c_void_p * V)(*[_ptr(d, "out_depth", c.width * c.height).value for (d, _), c in zip(out, cams)])
-    cptr = (ctypes.c_void_p * V)(*[_ptr(r, "out_rgb", 3 * c.width * c.height).value for (_, r), c in zip(out, cams)])
+    dptr = (ctypes.c_void_p * V)(*[_ptr(d, "out_depth", c.width * c.height) for (d, _), c in zip(out, cams)])
+    cptr = (ctypes.c_void_p * V)(*[_ptr(r, "out_rgb", 3 * c.width * c.height) for (_, r), c in zip(out, cams)])
     s = vol.struct()
     _check(lib().gps_raycast(ctypes.byref(s), carr, V, dptr, cptr, float(z_near), float(step), _stream(stream)),
            "gps_raycast")
@@ -455,8 +454,8 @@ def hash_raycast(vol: HashVolume, cams, z_near=0.2, step=0.0, out=None, stream=N
         out = [(torch.empty(c.height, c.width, dtype=torch.float32, device=vol.tsdf.device),
                 torch.empty(3, c.height, c.width, dtype=torch.float32, device=vol.tsdf.device)) for c in cams]
     carr = (Camera * V)(*cams)
-    dptr = (ctypes.c_void_p * V)(*[_ptr(d, "out_depth", c.width * c.height).value for (d, _), c in zip(out, cams)])
-    cptr = (ctypes.c_void_p * V)(*[_ptr(r, "out_rgb", 3 * c.width * c.height).value for (_, r), c in zip(out, cams)])
+    dptr = (ctypes.c_void_p * V)(*[_ptr(d, "out_depth", c.width * c.height) for (d, _), c in zip(out, cams)])
+    cptr = (ctypes.c_void_p * V)(*[_ptr(r, "out_rgb", 3 * c.width * c.height) for (_, r), c in zip(out, cams)])
     s = vol.struct()
     rng = None
     if range_scratch is True:
@@ -612,9 +611,9 @@ def views_upload(cfg: RenderCfg, gauss: dict, views, ws: Workspace, dL_drgb=None
     V = len(views)
     rgb_arr = dep_arr = None
     if dL_drgb is not None:
-        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb").value for t in dL_drgb])
+        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb") for t in dL_drgb])
         if dL_ddepth is not None:
-            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth").value if t is not None else None
+            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth")
                                              for t in dL_ddepth])
     _check(lib().gps_views_upload(ctypes.byref(cs), ctypes.byref(gs), va, V, rgb_arr, dep_arr, ws.ptr(), ws.nbytes,
                                   _stream(stream)), "gps_views_upload")
@@ -631,9 +630,9 @@ def render_bwd(cfg: RenderCfg, gauss: dict, views, ws: Workspace, grads: dict, d
     V = len(views)
     rgb_arr = dep_arr = None
     if dL_drgb is not None:
-        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb").value for t in dL_drgb])
+        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb") for t in dL_drgb])
         if dL_ddepth is not None:
-            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth").value if t is not None else None
+            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth")
                                              for t in dL_ddepth])
     _check(lib().gps_render_bwd(ctypes.byref(cs), ctypes.byref(gs), va, V, rgb_arr, dep_arr,
                                 _ptr(loss_scale, "loss_scale", 1) if loss_scale is not None else None,
@@ -660,9 +659,9 @@ def render_bwd_adam(cfg: RenderCfg, gauss: dict, views, ws: Workspace, opt: "Ada
     V = len(views)
     rgb_arr = dep_arr = None
     if dL_drgb is not None:
-        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb").value for t in dL_drgb])
+        rgb_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_drgb") for t in dL_drgb])
         if dL_ddepth is not None:
-            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth").value if t is not None else None
+            dep_arr = (ctypes.c_void_p * V)(*[_ptr(t, "dL_ddepth")
                                              for t in dL_ddepth])
     opt.t += 1
     af = AdamFusedS(gaussians_struct(opt.m), gaussians_struct(opt.v), float(opt.lr["mean"]),
@@ -765,8 +764,8 @@ class RenderLoss(torch.autograd.Function):
         s = ctx.session
         mean, log_scale, quat, opacity_logit, rgb, xi, sh = ctx.saved_tensors
         g = {"mean": mean, "log_scale": log_scale, "quat": quat, "opacity_logit": opacity_logit, "rgb": rgb, "sh": sh}
-        grads = zeros_like_gaussians(g)
-        dpose = torch.zeros(len(s.views), 6, dtype=torch.float32, device=mean.device)
+        grads = _empty_like_gaussians(g)
+        dpose = torch.empty(len(s.views), 6, dtype=torch.float32, device=mean.device)
         scale = gloss.detach().to(torch.float32).reshape(1).contiguous()
         render_bwd(s.cfg, g, s.views, s.ws, grads, dpose, loss_scale=scale, pose_xi=xi)
         return (grads["mean"], grads["log_scale"], grads["quat"], grads["opacity_logit"], grads["rgb"],
@@ -796,8 +795,8 @@ class Render(torch.autograd.Function):
         s = ctx.session
         mean, log_scale, quat, opacity_logit, rgb, xi, sh = ctx.saved_tensors
         g = {"mean": mean, "log_scale": log_scale, "quat": quat, "opacity_logit": opacity_logit, "rgb": rgb, "sh": sh}
-        grads = zeros_like_gaussians(g)
-        dpose = torch.zeros(len(s.views), 6, dtype=torch.float32, device=mean.device)
+        grads = _empty_like_gaussians(g)
+        dpose = torch.empty(len(s.views), 6, dtype=torch.float32, device=mean.device)
         drgb, ddep = [], []
         for i, v in enumerate(s.views):
             gr, gd = gouts[2 * i], gouts[2 * i + 1]
@@ -817,19 +816,13 @@ def remove_gaussians(params: dict, companions=(), min_opacity=0.005, max_scale=0
     sets = [params] + list(companions)
     L = sh_degree(params)
     K = SH_COEFFS[L]
-    outs = [{k: torch.empty(GAUSS_ROWS[k], max(M, 1), dtype=torch.float32, device=dev) for k in GAUSS_KEYS}
-            for _ in sets]
+    rows = dict(GAUSS_ROWS)
     if L > 0:
-        for o in outs:
-            o["sh"] = torch.empty(3 * K, max(M, 1), dtype=torch.float32, device=dev)
+        rows["sh"] = 3 * K
+    outs = [{k: torch.empty(r * max(M, 1), dtype=torch.float32, device=dev) for k, r in rows.items()} for _ in sets]
     arr_in = (GaussiansS * len(sets))(*[gaussians_struct(s) for s in sets])
-    arr_out = (GaussiansS * len(sets))()
-    for i, o in enumerate(outs):
-        arr_out[i].count = M
-        for k in GAUSS_KEYS:
-            setattr(arr_out[i], k, ctypes.c_void_p(o[k].data_ptr()))
-        arr_out[i].sh_degree = L
-        arr_out[i].sh = ctypes.c_void_p(o["sh"].data_ptr()) if L > 0 else None
+    arr_out = (GaussiansS * len(sets))(*[
+        GaussiansS(M, *[o[k].data_ptr() for k in GAUSS_KEYS], L, o["sh"].data_ptr() if L > 0 else None) for o in outs])
     nbytes = ctypes.c_size_t(0)
     _check(lib().gps_removal_workspace_size(M, ctypes.byref(nbytes)), "gps_removal_workspace_size")
     ws = torch.empty(nbytes.value, dtype=torch.uint8, device=dev)
@@ -839,11 +832,10 @@ def remove_gaussians(params: dict, companions=(), min_opacity=0.005, max_scale=0
                                       ctypes.c_void_p(count.data_ptr()), ctypes.c_void_p(ws.data_ptr()),
                                       nbytes.value, _stream(stream)), "gps_remove_gaussians")
     n = int(count.item())
-    shaped = [{k: o[k].reshape(-1)[:GAUSS_ROWS[k] * n].view(GAUSS_ROWS[k], n) if GAUSS_ROWS[k] > 1
-               else o[k].reshape(-1)[:n] for k in GAUSS_KEYS} for o in outs]
+    shape = {k: (r, n) if r > 1 else (n,) for k, r in rows.items()}
     if L > 0:
-        for sh_, o in zip(shaped, outs):
-            sh_["sh"] = o["sh"].reshape(-1)[:3 * K * n].view(3, K, n)
+        shape["sh"] = (3, K, n)
+    shaped = [{k: t[:rows[k] * n].view(shape[k]) for k, t in o.items()} for o in outs]
     return shaped[0], shaped[1:], n
 
 
@@ -951,15 +943,18 @@ def icp_reduce_noalloc(prev_cam, prev_depth, level_cam, level_depth, pose, dist_
     return out_sys
 
 
+def _icp_step_args(prev_cam, prev_depth, level_cam, level_depth, pose, dist_thresh, ws: IcpWorkspace, stream):
+    pc, lc = camera(prev_cam), camera({**level_cam, "R": np.eye(3), "t": np.zeros(3)})
+    return (ctypes.byref(pc), _ptr(prev_depth, "prev_depth", pc.width * pc.height), ctypes.byref(lc),
+            _ptr(level_depth, "level_depth", lc.width * lc.height), _ptr(pose, "pose", 12), float(dist_thresh),
+            ws.sys.data_ptr(), ws.xi.data_ptr(), ws.buf.data_ptr(), ws.nbytes, _stream(stream))
+
+
 def icp_step(prev_cam, prev_depth, level_cam, level_depth, pose, dist_thresh, ws: IcpWorkspace, stream=None):
     """One Gauss-Newton step (gps_icp_step): the system into ws.sys, the pose updated in
     place, xi into ws.xi -- icp_reduce then icp_solve with one launch fewer."""
-    pc, lc = camera(prev_cam), camera({**level_cam, "R": np.eye(3), "t": np.zeros(3)})
-    _check(lib().gps_icp_step(ctypes.byref(pc), _ptr(prev_depth, "prev_depth", pc.width * pc.height),
-                              ctypes.byref(lc), _ptr(level_depth, "level_depth", lc.width * lc.height),
-                              _ptr(pose, "pose", 12), float(dist_thresh), ctypes.c_void_p(ws.sys.data_ptr()),
-                              ctypes.c_void_p(ws.xi.data_ptr()), ctypes.c_void_p(ws.buf.data_ptr()), ws.nbytes,
-                              _stream(stream)), "gps_icp_step")
+    _check(lib().gps_icp_step(*_icp_step_args(prev_cam, prev_depth, level_cam, level_depth, pose, dist_thresh, ws,
+                                              stream)), "gps_icp_step")
     return ws.sys
 
 
@@ -986,6 +981,8 @@ def icp_track(prev_cam, prev_depth, cur_cam, cur_depth, pose: torch.Tensor, iter
     for k in range(L):
         lvl = L - 1 - k
         lc = level_camera(cur_cam, lvl)
-        for _ in range(iters[k]):
-            icp_step(prev_cam, prev_depth, lc, pyramid[lvl], pose, dist_thresh[k], ws, stream)
+        if iters[k] > 0:
+            args = _icp_step_args(prev_cam, prev_depth, lc, pyramid[lvl], pose, dist_thresh[k], ws, stream)
+            for _ in range(iters[k]):
+                _check(lib().gps_icp_step(*args), "gps_icp_step")
     return pose
