@@ -132,7 +132,7 @@ typedef struct gps_view {
 typedef struct gps_render_cfg {
     int32_t tile_w, tile_h;  /* screen tile: 8x8, 16x16, 16x32 or 32x16            */
     int32_t batch;           /* Gaussians staged in LDS per step: 128, 256 or 512  */
-    int32_t pix_per_thread;  /* pixels per lane: 1, 2 or 4                         */
+    int32_t pix_per_thread;  /* pixels per lane: 1, 2 or 4 (small grids take 1)    */
     int32_t mode;            /* 0 sorted over-compositing (the default); 1 the
                                 sort-free blend of Eq. 1, 2, 4                     */
     float eps_cull;          /* epsilon of the depth test of Eq. 1-2 (m)           */

@@ -201,6 +201,20 @@ __device__ __forceinline__ unsigned int wave_support_mask(const float4& r0, cons
 // Tile configurations (tile width, height, staged batch, pixels per lane) for
 // which both compositing kernels are instantiated.  A 32-pixel-wide tile reads
 // each row of a float image plane as one whole 128-byte line.
+// Small grids take one pixel per lane whatever the configuration asks: below 10 to 16 wavefronts
+// a SIMD (at one pixel a lane) what bounds the compositing is the longest list, which a
+// wavefront walks in fewer instructions the fewer pixels its lanes have.  Forward / backward in
+// us with two pixels and with one, 100 k Gaussians, tiles of 16x32: 640x480 105 / 178 and 68 / 140,
+// 1120x630 (11200 wavefronts) 82 / 135 and 65 / 132 (32x16: 96 / 152 and 65 / 156), 1280x720 (14720)
+// 81 / 139 and 74 / 152, 1600x900 (23200) 88 / 174 and 104 / 200; of 16x16: 1280x720 (14400)
+// 72 / 164 and 65 / 155, 1600x900 (22800) 88 / 214 and 87 / 210.
+constexpr long long kSmallGrid = 16384, kSmallGridBwd = 10240;  // (the latter for tiles of 512 pixels)
+
+inline bool one_pixel_per_lane(const gps_render_cfg* cfg, int n_tiles, long long few_waves)
+{
+    return cfg->pix_per_thread > 1 && (long long)n_tiles * cfg->tile_w * cfg->tile_h / 64 <= few_waves;
+}
+
 #define GPS_TILE_CONFIGS(X) \
     X(8, 8, 128, 1)         \
     X(8, 8, 256, 1)         \
