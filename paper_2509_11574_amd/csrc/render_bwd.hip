@@ -22,7 +22,8 @@ namespace gps {
 
 // ------------------------------------------------------------- gauss bwd
 constexpr unsigned int kCoopSlots = kKeptBits;  // more slots than this: summed by the whole wavefront
-constexpr unsigned int kSlotGroup = 8;   // slots loaded together by one lane
+constexpr unsigned int kSlotGroup = 4;   // slots loaded together by one lane (8: two wavefronts a SIMD instead
+                                         // of three, 220 us against 206 for 1 M Gaussians in four views)
 
 // EWA chain rule of one Gaussian in one view.  The summed instance partials are
 // first turned into A[10] = dL/d(mx, my, a, b, c), sigma dL/dsigma, dL/d(r, g, b, d),
@@ -365,10 +366,14 @@ __global__ void __launch_bounds__(kBlk) k_gauss_bwd(const ViewTable* __restrict_
             pose[5] = x * gpy - y * gpx + 2.0f * K[3];
         }
         // block partial of the pose gradient of view v (fixed order)
+        if (__builtin_amdgcn_ballot_w64(cnt > 0)) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const float t = wave_sum(pose[q]);
-            if ((threadIdx.x & 63) == 0) pred[threadIdx.x >> 6][q] = t;
+            for (int q = 0; q < 6; ++q) {
+                const float t = wave_sum(pose[q]);
+                if (lane == 0) pred[threadIdx.x >> 6][q] = t;
+            }
+        } else if (lane < 6) {  // no Gaussian of this wavefront is seen
+            pred[threadIdx.x >> 6][lane] = 0.0f;
         }
         __syncthreads();
         if (threadIdx.x < 6) {
@@ -415,14 +420,27 @@ __global__ void __launch_bounds__(kBlk) k_gauss_bwd(const ViewTable* __restrict_
                 af.v[a][i] = av[j];
             }
         if constexpr (SHK > 0) {
+            // A channel's parameters and moments are loaded together before any is stored (the
+            // stores may alias them for all the compiler knows, and row by row every load
+            // waited behind a store: SH degree 3, 50 k Gaussians 39 us, so 27).
 #pragma unroll
-            for (int r = 0; r < 3 * SHK; ++r) {
-                const size_t i = (size_t)r * M + g;
-                float p = af.p[5][i], m = af.m[5][i], v = af.v[5][i];
-                adam_one(p, gsh[r], m, v, af.lr[5], af.b1, af.b2, af.eps, ibc1, ibc2);
-                af.p[5][i] = p;
-                af.m[5][i] = m;
-                af.v[5][i] = v;
+            for (int ch = 0; ch < 3; ++ch) {
+                float p[SHK], m[SHK], v[SHK];
+#pragma unroll
+                for (int k = 0; k < SHK; ++k) {
+                    const size_t i = (size_t)(ch * SHK + k) * M + g;
+                    p[k] = af.p[5][i];
+                    m[k] = af.m[5][i];
+                    v[k] = af.v[5][i];
+                }
+#pragma unroll
+                for (int k = 0; k < SHK; ++k) {
+                    const size_t i = (size_t)(ch * SHK + k) * M + g;
+                    adam_one(p[k], gsh[ch * SHK + k], m[k], v[k], af.lr[5], af.b1, af.b2, af.eps, ibc1, ibc2);
+                    af.p[5][i] = p[k];
+                    af.m[5][i] = m[k];
+                    af.v[5][i] = v[k];
+                }
             }
         }
     }
@@ -440,12 +458,17 @@ __global__ void __launch_bounds__(256) k_pose_reduce(const ViewTable* __restrict
     // strides), per wavefront (DPP), then over the four wavefronts in order.
     const int v = blockIdx.x, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     __shared__ float red[4][6];
+    float t[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nblk; b += 256) {
+        const float* p = w.pose_part + ((size_t)b * rp.V + v) * 6;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) t[q] += p[q];
+    }
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        float t = 0.0f;
-        for (int b = threadIdx.x; b < nblk; b += 256) t += w.pose_part[((size_t)b * rp.V + v) * 6 + q];
-        t = wave_sum(t);
-        if (lane == 0) red[wid][q] = t;
+        const float r = wave_sum(t[q]);
+        if (lane == 0) red[wid][q] = r;
     }
     __syncthreads();
     const float* xi = vtp->v[v].pose_xi;

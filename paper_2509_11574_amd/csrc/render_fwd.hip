@@ -995,12 +995,18 @@ __global__ void __launch_bounds__(1024) k_loss_reduce(const ViewTable* __restric
     // summed per lane, then per wavefront (DPP), then over the wavefronts in order
     // by one thread: one barrier for all views.
     __shared__ float4 red[GPS_MAX_VIEWS][16];
+    unsigned long long pe = 0ull, pc = 0ull;
+    const bool counted = w.hdr->n_inst <= rp.cap;  // else no tile was composited
     for (int v = 0; v < vt.n; ++v) {
         const DevView& V = vt.v[v];
         const int nt = V.tiles_x * V.tiles_y;
         float a = 0.0f, b = 0.0f, c = 0.0f;
+#pragma unroll 2
         for (int t = threadIdx.x; t < nt; t += 1024) {
             const float4 q = w.tile_loss[V.tile_base + t];
+            const uint2 n = w.tile_pairs[V.tile_base + t];
+            pe += n.x;
+            pc += n.y;
             a += q.x;
             b += q.y;
             c += q.z;
@@ -1010,16 +1016,8 @@ __global__ void __launch_bounds__(1024) k_loss_reduce(const ViewTable* __restric
         c = wave_sum(c);
         if (lane == 0) red[v][wid] = make_float4(a, b, c, 0.0f);
     }
-    // Evaluated / composited pair counts of this forward, summed over the tiles in
-    // a fixed order and added to the cumulative counters of the header.
-    unsigned long long pe = 0ull, pc = 0ull;
-    if (w.hdr->n_inst <= rp.cap) {
-        for (int t = threadIdx.x; t < vt.n_tiles; t += 1024) {
-            const uint2 q = w.tile_pairs[t];
-            pe += q.x;
-            pc += q.y;
-        }
-    }
+    // Evaluated / composited pair counts of this forward, added to the cumulative
+    // counters of the header.
     for (int o = 32; o > 0; o >>= 1) {
         pe += __shfl_xor(pe, o, 64);
         pc += __shfl_xor(pc, o, 64);
@@ -1030,29 +1028,38 @@ __global__ void __launch_bounds__(1024) k_loss_reduce(const ViewTable* __restric
         spc[wid] = pc;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float L = 0.0f;
-        for (int v = 0; v < vt.n; ++v) {
-            float a = 0.0f, b = 0.0f, c = 0.0f;
-            for (int k = 0; k < 16; ++k) {
-                a += red[v][k].x;
-                b += red[v][k].y;
-                c += red[v][k].z;
-            }
-            w.hdr->view_stats[v][0] = a;
-            w.hdr->view_stats[v][1] = b;
-            w.hdr->view_stats[v][2] = c;
-            w.hdr->view_stats[v][3] = 0.0f;
-            const float npx = 3.0f * (float)vt.v[v].cam.W * (float)vt.v[v].cam.H;
-            L += a / npx + (c > 0.0f ? rp.lambda * b / c : 0.0f);
+    if (wid != 0) return;
+    // one lane per view, then one for all, in order
+    float Lv = 0.0f;
+    if (lane < vt.n) {
+        float a = 0.0f, b = 0.0f, c = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float4 q = red[lane][k];
+            a += q.x;
+            b += q.y;
+            c += q.z;
         }
+        w.hdr->view_stats[lane][0] = a;
+        w.hdr->view_stats[lane][1] = b;
+        w.hdr->view_stats[lane][2] = c;
+        w.hdr->view_stats[lane][3] = 0.0f;
+        const float npx = 3.0f * (float)vt.v[lane].cam.W * (float)vt.v[lane].cam.H;
+        Lv = a / npx + (c > 0.0f ? rp.lambda * b / c : 0.0f);
+    }
+    float L = 0.0f;
+    for (int v = 0; v < vt.n; ++v) L += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(Lv), v));
+    if (lane == 0) {
         unsigned long long te = 0ull, tc = 0ull;
+#pragma unroll
         for (int k = 0; k < 16; ++k) {
             te += spe[k];
             tc += spc[k];
         }
-        w.hdr->pairs_eval += te;
-        w.hdr->pairs_contrib += tc;
+        if (counted) {
+            w.hdr->pairs_eval += te;
+            w.hdr->pairs_contrib += tc;
+        }
         L = L / (float)vt.n;
         w.hdr->loss = has_loss ? L : 0.0f;
         if (out_loss && has_loss) *out_loss = L;
