@@ -1,6 +1,6 @@
 // TSDF + colour fusion and SDF raycast (Sec. 3.1 first pass, Sec. 3.2.1).
 //
-// Fusion is one lane per lattice point, lanes along x so that the volume
+// Fusion is one lane per lattice point in view, lanes along x so that the volume
 // arrays stream coalesced; only points in the frustum with a valid depth
 // sample read and write the volume, so traffic is 8 B/point outside the
 // truncation band and 32 B/point inside it (read + write).
@@ -22,25 +22,92 @@
 namespace gps {
 
 // ----------------------------------------------------------------- fusion
+// A cell is 2^lx x 2^(6-lx) lattice points of a z plane, one per lane.  A block takes 64 cells from
+// all over the lattice (the ones in view are neighbours: consecutive cells give blocks of 64
+// and blocks of none): its first wavefront tests, a lane each, whether they lie outside the view, and
+// all its wavefronts then fuse the others in turn.  A lane per point executed about 90
+// instructions a wavefront for every point of the lattice; what is left is bound by the
+// three dependent loads of a point.  256^3 points, 1280x720 frame: 21 us, without the test 39, with
+// consecutive cells 35, with 16 wavefronts a block 24.
+constexpr int kFuseWaves = 8;
+
 struct FuseArgs {
     FuseCtx ctx;
     int nx, ny;
     unsigned int N;
+    int lx;                     // log2 of a cell's width
+    unsigned int cx, cy, cells;  // cells along x, along y, in all
     float* tsdf;
     float* w;
     float* col;
     float* cw;
 };
 
-__global__ void __launch_bounds__(256) k_fuse(FuseArgs a)
+// No point of [x0, x1] x [y0, y1] x {z} projects into the image: it is behind the camera, or
+// beyond one border of it, at all four corners, by more than the rounding of fuse_point's
+// coordinates (below 1e-6 of the sums' magnitude) and of its pixel (below a hundredth and 1e-6 of the
+// image): the functions are linear, so all points between are too.  False for anything not finite.
+__device__ __forceinline__ bool fuse_outside(const FuseCtx& a, int x0, int x1, int y0, int y1, int z)
 {
-    const unsigned int idx = blockIdx.x * 256u + threadIdx.x;
-    if (idx >= a.N) return;
-    const unsigned int x = idx % (unsigned)a.nx;
-    const unsigned int r = idx / (unsigned)a.nx;
-    const unsigned int y = r % (unsigned)a.ny;
-    const unsigned int z = r / (unsigned)a.ny;
-    fuse_point(a.ctx, (int)x, (int)y, (int)z, idx, a.N, a.tsdf, a.w, a.col, a.cw);
+    const DevCam& c = a.cam;
+    const float px[2] = {a.ox + a.voxel * (float)x0, a.ox + a.voxel * (float)x1};
+    const float py[2] = {a.oy + a.voxel * (float)y0, a.oy + a.voxel * (float)y1};
+    const float pz = a.oz + a.voxel * (float)z;
+    float m = 0.0f, tz = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) m = fmaxf(m, fabsf(c.R[k]));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tz = fmaxf(tz, fabsf(c.t[k]));
+    const float reach = fmaxf(fabsf(px[0]), fabsf(px[1])) + fmaxf(fabsf(py[0]), fabsf(py[1])) + fabsf(pz) + fabsf(a.ox) +
+                        fabsf(a.oy) + fabsf(a.oz);  // (a point's own rounding is relative to its origin's too)
+    const float e = 4e-6f * (m * reach + tz);
+    const float W = (float)c.W, H = (float)c.H;
+    const float du = 0.01f + 1e-6f * (fabsf(c.cx) + W), dv = 0.01f + 1e-6f * (fabsf(c.cy) + H);
+    const float kl = c.cx + 0.5f + du, kr = c.cx + 0.5f - W - du, kt = c.cy + 0.5f + dv, kb = c.cy + 0.5f - H - dv;
+    const float eu = e * (fabsf(c.fx) + fabsf(c.cx) + W + 2.0f), ev = e * (fabsf(c.fy) + fabsf(c.cy) + H + 2.0f);
+    bool behind = true, left = true, right = true, top = true, bottom = true;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float X = px[k & 1], Y = py[k >> 1];
+        const float xc = c.R[0] * X + c.R[1] * Y + c.R[2] * pz + c.t[0];
+        const float yc = c.R[3] * X + c.R[4] * Y + c.R[5] * pz + c.t[1];
+        const float zc = c.R[6] * X + c.R[7] * Y + c.R[8] * pz + c.t[2];
+        behind = behind && zc < -e;
+        left = left && c.fx * xc + kl * zc < -eu;
+        right = right && c.fx * xc + kr * zc > eu;
+        top = top && c.fy * yc + kt * zc < -ev;
+        bottom = bottom && c.fy * yc + kb * zc > ev;
+    }
+    return behind || left || right || top || bottom;
+}
+
+__global__ void __launch_bounds__(64 * kFuseWaves) k_fuse(FuseArgs a)
+{
+    __shared__ int4 cell[64];
+    __shared__ int n_seen;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int wx = 1 << a.lx, wy = 64 >> a.lx;
+    if (wid == 0) {
+        const unsigned int c = lane * gridDim.x + blockIdx.x, r = c / a.cx;
+        const int x0 = (int)(c - r * a.cx) << a.lx, z = (int)(r / a.cy);
+        const int y0 = (int)(r - (unsigned int)z * a.cy) * wy;
+        const bool seen = c < a.cells && !fuse_outside(a.ctx, x0, min(x0 + wx, a.nx) - 1, y0, min(y0 + wy, a.ny) - 1, z);
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(seen);
+        if (seen)
+            cell[__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u))] =
+                make_int4(x0, y0, z, 0);
+        if (lane == 0) n_seen = (int)__builtin_popcountll(m);
+    }
+    __syncthreads();
+    const int n = n_seen;
+    for (int k = wid; k < n; k += kFuseWaves) {
+        const int4 c = cell[k];
+        const int x = c.x + (lane & (wx - 1)), y = c.y + (lane >> a.lx);
+        if (x < a.nx && y < a.ny) {
+            const unsigned int idx = ((unsigned int)c.z * (unsigned int)a.ny + (unsigned int)y) * (unsigned int)a.nx + (unsigned int)x;
+            fuse_point(a.ctx, x, y, c.z, idx, a.N, a.tsdf, a.w, a.col, a.cw);
+        }
+    }
 }
 
 gps_status launch_fuse(const gps_volume* vol, const gps_camera* cam, const float* depth, const float* rgb,
@@ -63,8 +130,14 @@ gps_status launch_fuse(const gps_volume* vol, const gps_camera* cam, const float
     a.w = vol->weight;
     a.col = vol->rgb;
     a.cw = vol->rgb_weight;
-    unsigned int blocks = (a.N + 255u) / 256u;
-    GPS_LAUNCH(K_FUSE, s, k_fuse, dim3(blocks), dim3(256), 0, s, a);
+    // The widest cell that leaves at most a quarter of its lanes beyond the rows' ends.
+    a.lx = 6;
+    while (a.lx > 1 && 4ll * a.nx < 3ll * (((a.nx + (1 << a.lx) - 1) >> a.lx) << a.lx)) --a.lx;
+    a.cx = (unsigned int)((a.nx + (1 << a.lx) - 1) >> a.lx);
+    a.cy = (unsigned int)((a.ny + (64 >> a.lx) - 1) / (64 >> a.lx));
+    a.cells = a.cx * a.cy * (unsigned int)vol->nz;
+    const unsigned int blocks = (a.cells + 63u) / 64u;
+    GPS_LAUNCH(K_FUSE, s, k_fuse, dim3(blocks), dim3(64 * kFuseWaves), 0, s, a);
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 
