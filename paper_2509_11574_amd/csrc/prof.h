@@ -11,7 +11,6 @@ enum KernelId {
     K_FUSE = 0,
     K_BRICK_MIN,
     K_RAYCAST,
-    K_TILEMAX,
     K_PROJECT,
     K_SCAN,
     K_SCAN_TILES,

@@ -4,8 +4,8 @@
 //
 // Kernel sequence (one launch each, all grids sized from host-known shapes,
 // so the sequence is graph-capturable):
-//   k_tilemax      per screen tile: max of the SDF depth (invalid = +inf); launched
-//                  with the view-table upload, not per forward
+//   k_upload_views view table and, per screen tile, max of the SDF depth (invalid = +inf);
+//                  at an upload, not per forward
 //   k_project      per (view, Gaussian): projected record, the number of screen tiles its
 //                  support box covers (one slot per tile), and per block and tile the
 //                  count of the instances that pass the exact culls
@@ -26,32 +26,6 @@
 #include "se3.h"
 
 namespace gps {
-
-// ---------------------------------------------------- tile depth maxima
-// Per screen tile: the maximum of the SDF base depth (invalid = +inf), taken
-// when the view table is uploaded (the base images are fixed until the next upload).
-__global__ void __launch_bounds__(256) k_tilemax(const ViewTable* __restrict__ vtp, RParams rp, WsPtrs w)
-{
-    const ViewTable& vt = *vtp;
-    const int tile = blockIdx.x;
-    const int v = find_view(vt, tile);
-    const DevView& V = vt.v[v];
-    const int lt = tile - V.tile_base;
-    const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
-    float m = -INFINITY;
-    for (int k = threadIdx.x; k < rp.tile_w * rp.tile_h; k += 256) {
-        int x = tx * rp.tile_w + k % rp.tile_w, y = ty * rp.tile_h + k / rp.tile_w;
-        if (x < V.cam.W && y < V.cam.H) {
-            float d = V.base_depth[(size_t)y * V.cam.W + x];
-            m = fmaxf(m, d > 0.0f ? d : INFINITY);
-        }
-    }
-    m = wave_max(m);
-    __shared__ float red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) w.tilemax[tile] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
 
 // ---------------------------------------------------------------- project
 // EWA projection of one Gaussian into one view (Eq. 3; 3DGS convention):
@@ -1067,39 +1041,61 @@ __global__ void __launch_bounds__(1024) k_loss_reduce(const ViewTable* __restric
 }
 
 // ------------------------------------------------------------ view table
-// Copies the by-value view table into the workspace, so that a replayed
-// sequence of kernels reads whatever table was uploaded last.
-// A view with pose_xi is written with the camera Exp(xi) T_cw (binary64
-// composition, rounded once to binary32).
-__global__ void __launch_bounds__(256) k_upload_views(ViewTable vt, ViewTable* dst)
+// Copies the by-value view table into the workspace (the first block), so that a replayed
+// sequence of kernels reads whatever table was uploaded last.  A view with pose_xi is written
+// with the camera Exp(xi) T_cw (binary64 composition, rounded once to binary32).
+// Then (one block per tile) the tile depth maxima: the maximum of the SDF base depth over each
+// screen tile (invalid = +inf; the base images are fixed until the next upload).  They need nothing
+// that pose_xi changes, so both are one launch and read the table in the kernel's arguments.
+__global__ void __launch_bounds__(256) k_upload_views(ViewTable vt, ViewTable* dst, RParams rp, float* tilemax)
 {
-    const unsigned int* src = reinterpret_cast<const unsigned int*>(&vt);
-    unsigned int* d = reinterpret_cast<unsigned int*>(dst);
-    for (int i = threadIdx.x; i < (int)(sizeof(ViewTable) / 4); i += 256) d[i] = src[i];
-    __syncthreads();
-    const int v = threadIdx.x;
-    if (v < vt.n && vt.v[v].pose_xi) {
-        double xi[6], E[9], e[3];
-        for (int k = 0; k < 6; ++k) xi[k] = (double)vt.v[v].pose_xi[k];
-        se3_exp_d(xi, E, e);
-        const DevCam& c = vt.v[v].cam;
-        DevCam& o = dst->v[v].cam;
-        for (int r = 0; r < 3; ++r) {
-            for (int k = 0; k < 3; ++k)
-                o.R[3 * r + k] = (float)(E[3 * r] * c.R[k] + E[3 * r + 1] * c.R[3 + k] + E[3 * r + 2] * c.R[6 + k]);
-            o.t[r] = (float)(E[3 * r] * c.t[0] + E[3 * r + 1] * c.t[1] + E[3 * r + 2] * c.t[2] + e[r]);
+    if (blockIdx.x == 0) {
+        const unsigned int* src = reinterpret_cast<const unsigned int*>(&vt);
+        unsigned int* d = reinterpret_cast<unsigned int*>(dst);
+        for (int i = threadIdx.x; i < (int)(sizeof(ViewTable) / 4); i += 256) d[i] = src[i];
+        __syncthreads();
+        const int v = threadIdx.x;
+        if (v < vt.n && vt.v[v].pose_xi) {
+            double xi[6], E[9], e[3];
+            for (int k = 0; k < 6; ++k) xi[k] = (double)vt.v[v].pose_xi[k];
+            se3_exp_d(xi, E, e);
+            const DevCam& c = vt.v[v].cam;
+            DevCam& o = dst->v[v].cam;
+            for (int r = 0; r < 3; ++r) {
+                for (int k = 0; k < 3; ++k)
+                    o.R[3 * r + k] = (float)(E[3 * r] * c.R[k] + E[3 * r + 1] * c.R[3 + k] + E[3 * r + 2] * c.R[6 + k]);
+                o.t[r] = (float)(E[3 * r] * c.t[0] + E[3 * r + 1] * c.t[1] + E[3 * r + 2] * c.t[2] + e[r]);
+            }
         }
     }
+    if (!tilemax) return;
+    const int tile = blockIdx.x;
+    const int v = find_view(vt, tile);
+    const int W = vt.v[v].cam.W, H = vt.v[v].cam.H, lt = tile - vt.v[v].tile_base, tiles_x = vt.v[v].tiles_x;
+    const float* depth = vt.v[v].base_depth;
+    const int tx = lt % tiles_x, ty = lt / tiles_x;
+    float m = -INFINITY;
+    for (int k = threadIdx.x; k < rp.tile_w * rp.tile_h; k += 256) {
+        const int x = tx * rp.tile_w + k % rp.tile_w, y = ty * rp.tile_h + k / rp.tile_w;
+        if (x < W && y < H) {
+            const float d = depth[(size_t)y * W + x];
+            m = fmaxf(m, d > 0.0f ? d : INFINITY);
+        }
+    }
+    m = wave_max(m);
+    __shared__ float red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) tilemax[tile] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// The table upload, then (with_tilemax) the tile depth maxima of its views.
+// The table upload, with (with_tilemax) the tile depth maxima of its views.
 gps_status launch_views_upload(const ViewTable& vt, const RParams& rp, const WsLayout& L, char* ws, int with_tilemax,
                                hipStream_t s)
 {
     ViewTable* dvt = reinterpret_cast<ViewTable*>(ws + L.vtab);
-    GPS_LAUNCH(K_UPLOAD, s, k_upload_views, dim3(1), dim3(256), 0, s, vt, dvt);
-    if (with_tilemax && L.n_tiles > 0)
-        GPS_LAUNCH(K_TILEMAX, s, k_tilemax, dim3(L.n_tiles), dim3(256), 0, s, dvt, rp, ws_ptrs(ws, L));
+    float* tilemax = with_tilemax ? ws_ptrs(ws, L).tilemax : nullptr;
+    GPS_LAUNCH(K_UPLOAD, s, k_upload_views, dim3(with_tilemax ? L.n_tiles : 1), dim3(256), 0, s, vt, dvt, rp, tilemax);
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 
