@@ -83,22 +83,23 @@ __device__ __forceinline__ float row_sum(float x)
 }
 
 // Sums of 32 values over the wavefront: row r (lanes 16 r .. 16 r + 15) gets in out[q] that of value
-// 4 q + 2 (r & 1) + (r >> 1), summed as x + (x of lane ^ 32, 16, 8, 4, 2, 1).  An exchange of halves
-// between two values sums both at once: 24 exchanges and 56 additions, where a shuffle through
-// LDS per step and value took 174 and most of the kernel's time.
+// 4 q + 2 (r & 1) + (r >> 1), summed as x + (x of lane ^ 32, 16, 8, 4, 2, 1).  Across halves and
+// rows a lane keeps one of two values and sends the other, so an exchange serves both: 24
+// shuffles through LDS, where one per step and value took 174 and most of the kernel's time.
+__device__ __forceinline__ float exchange_sum(float a, float b, bool second, int mask)
+{
+    const float keep = second ? b : a, send = second ? a : b;
+    return keep + __shfl_xor(send, mask, 64);
+}
+
 __device__ __forceinline__ void wave_sums32(const float (&v)[32], float (&out)[8])
 {
+    const int lane = threadIdx.x & 63;
     float h[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_int(v[2 * k]), __float_as_int(v[2 * k + 1]), false, false);
-        h[k] = __int_as_float((int)s[0]) + __int_as_float((int)s[1]);
-    }
+    for (int k = 0; k < 16; ++k) h[k] = exchange_sum(v[2 * k], v[2 * k + 1], (lane & 32) != 0, 32);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_int(h[2 * k]), __float_as_int(h[2 * k + 1]), false, false);
-        out[k] = row_sum(__int_as_float((int)s[0]) + __int_as_float((int)s[1]));
-    }
+    for (int k = 0; k < 8; ++k) out[k] = row_sum(exchange_sum(h[2 * k], h[2 * k + 1], (lane & 16) != 0, 16));
 }
 
 // n / d, correctly rounded, from r = 1 / d correctly rounded: the first correction leaves the
@@ -114,8 +115,8 @@ __device__ __forceinline__ float div_shared(float n, float d, float r)
     return __builtin_fmaf(__builtin_fmaf(-q, d, n), r, q);
 }
 
-// Focal lengths of ordinary size: between 2^-40 and 2^40, and a pixel offset is 0 or at least
-// 2^-40 then.
+// Focal lengths and principal points of ordinary size: a pixel's offset is then 0 or at least 2^-44,
+// and quotients and remainders stay far from the smallest numbers.
 static bool focal_sane(float f, float c)
 {
     const float m = std::fabs(f);

@@ -40,7 +40,7 @@ __device__ inline void se3_exp_d(const double xi[6], double R[9], double t[3])
 // is taken on the vector (ad^T (a, b) = -(phi x a, rho x a + phi x b): three cross products
 // a term) and not on the 6x6 matrix, and it ends once the rest is below binary64 rounding
 // of the sum; 39 terms, which reach |phi| = 2 pi, at most.  The matrix series took 66 us
-// a call (a 160x120 view as a 1280x720 one) and this one takes 5.
+// a call (a 160x120 view as a 1280x720 one) and this one takes 3 to 4.
 __device__ inline void se3_left_jacobian_t_mul_d(const double xi[6], const double g[6], double y[6])
 {
     const double rx = xi[0], ry = xi[1], rz = xi[2], px = xi[3], py = xi[4], pz = xi[5];
