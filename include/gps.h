@@ -176,11 +176,13 @@ typedef struct gps_render_cfg {
  * blend of Eq. 1, 2, 4 is independent of order).  Each tile's list is taken in
  * the order the binning emitted it, every record of the list is visited (no list
  * is cut short by the depth order), and the long-list sort is not launched.  The
- * emission order comes from atomic counters, so the order of the floating-point
- * sums -- and the last bits of C*, D* and W_G -- may differ between calls (the
- * only exception to the determinism of the other entry points); the gradients
- * differ from call to call only through those bits.  GPS_ERR_UNSUPPORTED_CONFIG
- * in mode 0. */
+ * list has four parts: group k of 64 consecutive view-Gaussians stands in part
+ * k mod 4.  Within a part the order comes from atomic counters, so the order of the
+ * floating-point sums -- and the last bits of C*, D* and W_G -- may differ between
+ * calls (the only exception to the determinism of the other entry points); the
+ * gradients differ from call to call only through those bits (which may decide the
+ * sign of an L1 adjoint whose residual is within them of zero).
+ * GPS_ERR_UNSUPPORTED_CONFIG in mode 0. */
 #define GPS_RENDER_NO_SORT 4
 
 /* One Adam parameter group. */

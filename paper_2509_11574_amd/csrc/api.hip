@@ -80,7 +80,7 @@ static gps_status compute_layout(const gps_render_cfg* cfg, int M, const gps_cam
     L->nvg = (int)nvg;
     L->nblk_g = (M + kBlk - 1) / kBlk;
     L->cap = cap;
-    L->bin = bin_shape(M, V, (size_t)n_tiles, (size_t)most_tiles, cap);
+    L->bin = bin_shape(M, V, (size_t)n_tiles, (size_t)most_tiles, cap, (cfg->flags & GPS_RENDER_NO_SORT) != 0);
     size_t o = 0;
     L->hdr = o;
     o = align_up(o + 1024);

@@ -40,10 +40,32 @@ constexpr size_t kMostRowWords = 4u << 20;   // of tile counts over all blocks (
 // lines, where a wavefront takes several anyway.
 constexpr int kRunFew = 8, kRunShort = 16, kRunLong = 64, kRunIters = 4;
 
-inline BinShape bin_shape(int M, int V, size_t n_tiles, size_t most_tiles, unsigned long long cap)
+// Where no sort follows, the places that the emission gives are the order in which every pixel adds its
+// Gaussians, so they decide the last bits of the images and, where a residual is within those bits of zero,
+// the sign of its L1 adjoint.  The order is this: group k of 64 consecutive view-Gaussians (numbered
+// over the views) takes its places in part k mod 4 of each tile's range, in each part as the
+// groups arrive.  So the blocks are single wavefronts over such groups (the ones in flight together a
+// multiple of kCntSplit), and kCntSplit shared rows the parts.  With LDS rows over the whole map a pass over
+// 70 k Gaussians at 953x617 takes 157 us, not 163, and each pixel adds in another order.
+constexpr int kOrderGroup = 64;
+
+inline BinShape bin_shape(int M, int V, size_t n_tiles, size_t most_tiles, unsigned long long cap,
+                          bool unsorted)
 {
-    BinShape b{0, kManyWaves, kManyPer, 0, kRunLong, 0, 0, 0};
+    BinShape b{0, kManyWaves, kManyPer, 0, kRunLong, 0, 0, 0, 0};
     if (M == 0) return b;
+    if (unsorted) {
+        // (a view's first group may begin in the view before)
+        const int wanted = (int)(((long long)M + 2 * (kOrderGroup - 1)) / kOrderGroup);
+        const int most = std::max(kMostWaves / V / kCntSplit, 1) * kCntSplit;
+        b.unsorted = 1;
+        b.waves = 1;
+        b.per = b.run = kOrderGroup;
+        b.rows = kCntSplit;
+        b.iters = (wanted + most - 1) / most;
+        b.chunks = ((wanted + b.iters - 1) / b.iters + kCntSplit - 1) / kCntSplit * kCntSplit;
+        return b;
+    }
     const bool few = (long long)M * V <= kFewGaussians;
     // The rows lie where the instance capacity has left room.  With much less room than blocks
     // wanted, the shared rows.

@@ -97,9 +97,10 @@ struct WsHeader {
 // wavefronts per view, a wavefront taking `per` Gaussians `iters` times, as runs of `run`
 // consecutive ones (see binning.h).  With `lds` a block counts its instances per tile in LDS
 // (`lds_words` counters) and has a row of tile counts of its own (rows = chunks); otherwise
-// the blocks of a view share `rows` rows in memory.
+// the blocks of a view share `rows` rows in memory.  With `unsorted` the share of a block is a
+// group of kOrderGroup consecutive view-Gaussians at a time.
 struct BinShape {
-    int chunks, waves, per, iters, run, rows, lds, lds_words;
+    int chunks, waves, per, iters, run, rows, lds, lds_words, unsorted;
 };
 
 struct WsLayout {

@@ -172,17 +172,31 @@ __device__ __forceinline__ unsigned int lanes_before(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
 }
 
-// The Gaussian of a lane in iteration i of a wavefront's share (M: none).
+// The Gaussian of a lane in iteration i of a wavefront's share (M: none).  skew: of the first group, those of
+// the view before.
 template <int PER>
-__device__ __forceinline__ int share_gaussian(const BinShape& bs, int chunk, int wid, int lane, int i, int M)
+__device__ __forceinline__ int share_gaussian(const BinShape& bs, int chunk, int wid, int lane, int i, int M,
+                                              unsigned int skew)
 {
     if (lane >= PER) return M;
     const unsigned int per = (unsigned int)(PER / bs.run);  // runs a wavefront takes at a time
     const unsigned long long waves = (unsigned long long)bs.chunks * bs.waves;
     const unsigned long long r = ((unsigned long long)i * per + (unsigned int)(lane / bs.run)) * waves +
                                  (unsigned int)(chunk * bs.waves + wid);
-    const unsigned long long g = r * bs.run + (unsigned int)(lane % bs.run);
+    const unsigned long long g = r * bs.run + (unsigned int)(lane % bs.run) - skew;  // (below 0: beyond M)
     return g < (unsigned long long)M ? (int)g : M;
+}
+
+// Where the shared rows are the parts of an unsorted list: the place of view v's first Gaussian in its
+// group, and the row of a block.
+__device__ __forceinline__ unsigned int group_skew(const BinShape& bs, int v, int M)
+{
+    return bs.unsorted ? (unsigned int)(v * M) % kOrderGroup : 0u;
+}
+
+__device__ __forceinline__ int shared_row(const BinShape& bs, int v, int chunk, int M)
+{
+    return (bs.unsorted ? chunk + v * M / kOrderGroup : chunk) % bs.rows;
 }
 
 // The slots of the window [w0, w0 + 64) of a walk: for this lane's slot its owner in the
@@ -261,7 +275,9 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_project(const ViewTable* __re
     const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
     const DevView& V = vt.v[v];
     const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
+    const unsigned int skew = LDS ? 0u : group_skew(bs, v, rp.M);
+    unsigned int* row =
+        w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : shared_row(bs, v, chunk, rp.M)) * n_tiles;
     CountWalk<PER>& ww = walk[wid];
     const float l2amin = __log2f(rp.amin);
     if (LDS) {
@@ -270,7 +286,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_project(const ViewTable* __re
     }
     unsigned long long slots = 0ull;
     for (int i = 0; i < bs.iters; ++i) {
-        const int g = share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
+        const int g = share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew);
         const size_t vg = (size_t)v * rp.M + g;
         unsigned int n = 0u, t0 = 0u, span = 0u, kept = 0u;
         ProjOut p;
@@ -600,14 +616,16 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
     const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
     const DevView& V = vt.v[v];
     const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
+    const unsigned int skew = LDS ? 0u : group_skew(bs, v, rp.M);
+    unsigned int* row =
+        w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : shared_row(bs, v, chunk, rp.M)) * n_tiles;
     const unsigned int* start = w.tile_start + V.tile_base;
     EmitWalk<PER>& ww = walk[wid];
     // A Gaussian's loads are issued an iteration ahead.
     unsigned int span = 0u, t0 = 0u, kept = 0u, span1 = 0u, t01 = 0u, kept1 = 0u;
     float z = 0.0f, z1 = 0.0f;
     auto load = [&](int i) {
-        const int g = i < bs.iters ? share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M) : rp.M;
+        const int g = i < bs.iters ? share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew) : rp.M;
         span1 = 0u;
         if (g < rp.M) {
             const size_t vg = (size_t)v * rp.M + g;
@@ -626,7 +644,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
     }
     const float l2amin = __log2f(rp.amin);
     for (int i = 0; i < bs.iters; ++i) {
-        const size_t vg = (size_t)v * rp.M + share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
+        const size_t vg = (size_t)v * rp.M + share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew);
         span = span1;
         t0 = t01;
         kept = kept1;
@@ -651,7 +669,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
                 const uint4 c = ww.c[owner];
                 int tx, ty;
                 const Slot s = slot_of<LDS>(c, w0 + lane, V.tiles_x, &tx, &ty);
-                const int owner_g = share_gaussian<PER>(bs, chunk, wid, (c.w >> 16) & 63, i, rp.M);
+                const int owner_g = share_gaussian<PER>(bs, chunk, wid, (c.w >> 16) & 63, i, rp.M, skew);
                 bool pass;
                 if (s.small) {
                     pass = (ww.kept[owner] >> s.j) & 1u;
@@ -1135,24 +1153,21 @@ gps_status launch_views_upload(const ViewTable& vt, const RParams& rp, const WsL
 }
 
 // ----------------------------------------------------------------- launch
-template <int WAVES, int PER>
+template <int WAVES, int PER, bool LDS>
 static void launch_project(const ViewTable* vt, const RParams& rp, const BinShape& bs, const GParams& gp, const WsPtrs& w,
                            hipStream_t s)
 {
     const dim3 grid((unsigned int)(bs.chunks * rp.V)), blk(64 * WAVES);
     const size_t lds = 4 * (size_t)bs.lds_words;
-    if (bs.lds && gp.sh_k) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, true, true>), grid, blk, lds, s, vt, rp, bs, gp, w);
-    else if (bs.lds) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, true, false>), grid, blk, lds, s, vt, rp, bs, gp, w);
-    else if (gp.sh_k) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, false, true>), grid, blk, 0, s, vt, rp, bs, gp, w);
-    else GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, false, false>), grid, blk, 0, s, vt, rp, bs, gp, w);
+    if (gp.sh_k) GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, LDS, true>), grid, blk, lds, s, vt, rp, bs, gp, w);
+    else GPS_LAUNCH(K_PROJECT, s, (k_project<WAVES, PER, LDS, false>), grid, blk, lds, s, vt, rp, bs, gp, w);
 }
 
-template <int WAVES, int PER>
+template <int WAVES, int PER, bool LDS>
 static void launch_emit(const ViewTable* vt, const RParams& rp, const BinShape& bs, const WsPtrs& w, hipStream_t s)
 {
     const dim3 grid((unsigned int)(bs.chunks * rp.V)), blk(64 * WAVES);
-    if (bs.lds) GPS_LAUNCH(K_EMIT, s, (k_emit<WAVES, PER, true>), grid, blk, 4 * (size_t)bs.lds_words, s, vt, rp, bs, w);
-    else GPS_LAUNCH(K_EMIT, s, (k_emit<WAVES, PER, false>), grid, blk, 0, s, vt, rp, bs, w);
+    GPS_LAUNCH(K_EMIT, s, (k_emit<WAVES, PER, LDS>), grid, blk, 4 * (size_t)bs.lds_words, s, vt, rp, bs, w);
 }
 
 gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const gps_gaussians* g,
@@ -1177,8 +1192,11 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
             GPS_LAUNCH(K_SCAN, s, k_zero_rows, dim3((unsigned int)std::min((n + kBlk - 1) / kBlk, (size_t)1024)),
                        dim3(kBlk), 0, s, w, n);
         }
-        if (bs.per == kFewPer) launch_project<kFewWaves, kFewPer>(dvt, rp, bs, gp, w, s);
-        else launch_project<kManyWaves, kManyPer>(dvt, rp, bs, gp, w, s);
+        if (bs.unsorted) launch_project<1, kOrderGroup, false>(dvt, rp, bs, gp, w, s);
+        else if (bs.per == kFewPer && bs.lds) launch_project<kFewWaves, kFewPer, true>(dvt, rp, bs, gp, w, s);
+        else if (bs.per == kFewPer) launch_project<kFewWaves, kFewPer, false>(dvt, rp, bs, gp, w, s);
+        else if (bs.lds) launch_project<kManyWaves, kManyPer, true>(dvt, rp, bs, gp, w, s);
+        else launch_project<kManyWaves, kManyPer, false>(dvt, rp, bs, gp, w, s);
     }
     if (bs.rows <= kSmallRows && L.n_tiles <= kSmallTiles) {
         GPS_LAUNCH(K_SCAN, s, k_scan_small, dim3(1), dim3(1024), 0, s, dvt, rp, bs, w, L.n_tiles);
@@ -1188,8 +1206,11 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
         else GPS_LAUNCH(K_SCAN_TILES, s, k_scan_tiles<8>, dim3(1), dim3(1024), 0, s, rp, w, L.n_tiles);
     }
     if (bs.chunks > 0) {
-        if (bs.per == kFewPer) launch_emit<kFewWaves, kFewPer>(dvt, rp, bs, w, s);
-        else launch_emit<kManyWaves, kManyPer>(dvt, rp, bs, w, s);
+        if (bs.unsorted) launch_emit<1, kOrderGroup, false>(dvt, rp, bs, w, s);
+        else if (bs.per == kFewPer && bs.lds) launch_emit<kFewWaves, kFewPer, true>(dvt, rp, bs, w, s);
+        else if (bs.per == kFewPer) launch_emit<kFewWaves, kFewPer, false>(dvt, rp, bs, w, s);
+        else if (bs.lds) launch_emit<kManyWaves, kManyPer, true>(dvt, rp, bs, w, s);
+        else launch_emit<kManyWaves, kManyPer, false>(dvt, rp, bs, w, s);
     }
     if (rp.mode != 2)  // the unsorted sort-free blend keeps the emission order
         GPS_LAUNCH(K_TILE_SORT_LARGE, s, k_tile_sort_large, dim3(L.n_tiles < kSortGrid ? L.n_tiles : kSortGrid),
