@@ -132,7 +132,9 @@ typedef struct gps_view {
 typedef struct gps_render_cfg {
     int32_t tile_w, tile_h;  /* screen tile: 8x8, 16x16, 16x32 or 32x16            */
     int32_t batch;           /* Gaussians staged in LDS per step: 128, 256 or 512  */
-    int32_t pix_per_thread;  /* pixels per lane: 1, 2 or 4 (small grids take 1)    */
+    int32_t pix_per_thread;  /* pixels per lane: 1, 2 or 4.  Above 1, small grids
+                                run with 1 and a batch of their own
+                                (gps_render_composite_cfg)                         */
     int32_t mode;            /* 0 sorted over-compositing (the default); 1 the
                                 sort-free blend of Eq. 1, 2, 4                     */
     float eps_cull;          /* epsilon of the depth test of Eq. 1-2 (m)           */
@@ -224,6 +226,14 @@ void gps_render_cfg_default(gps_render_cfg* cfg);
  * nothing launched).  cams: host array of n_views cameras. */
 gps_status gps_workspace_size(const gps_render_cfg* cfg, int32_t n_gaussians, const gps_camera* cams,
                               int32_t n_views, size_t* out_bytes);
+
+/* The configurations that the compositing of a forward and of a (per-tile) backward run with: cfg,
+ * with another batch and one pixel per lane where cfg asks for more and the grid is
+ * small (few tiles, or few for its Gaussians).  Images are the same bits with any
+ * configuration of a tile shape in the sorted modes; gradients are the same sums in
+ * another order, and the statistics' evaluated pairs are those of the forward that ran. */
+gps_status gps_render_composite_cfg(const gps_render_cfg* cfg, int32_t n_gaussians, const gps_camera* cams,
+                                    int32_t n_views, gps_render_cfg* out_fwd, gps_render_cfg* out_bwd);
 
 /* Clears the workspace header (sticky status, counters, Adam step counter).
  * Call once after allocating a workspace, and after a capacity error before

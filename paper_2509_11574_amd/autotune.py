@@ -1,11 +1,13 @@
 """Autotuner for the compositing kernels: screen tile (8x8, 16x16, 16x32, 32x16) x
 Gaussians staged per LDS batch (128, 256, 512) x pixels per lane (1, 2, 4).
 
-Every combination compiled into libgps is timed on the caller's real workload
+The combinations compiled into libgps are timed on the caller's real workload
 (render forward + backward on the given views), with HIP events on the current
 stream; the fastest is returned and cached per (device architecture, view
-sizes, Gaussian count bucket, mode).  All combinations compute the same
-function; they differ only in summation order and speed.
+sizes, Gaussian count bucket, mode).  Combinations that run as the same kernels
+(gps.composite_cfgs: small grids take one pixel per lane) are timed once and have
+the one time.  All combinations compute the same function; they differ only in
+summation order and speed.
 """
 from __future__ import annotations
 
@@ -89,10 +91,13 @@ def autotune(cfg: G.RenderCfg, params: dict, views, configs=None, reps: int = 5,
         tw, th, b, ppt = db[key]["best"]
         return replace(cfg, tile_w=tw, tile_h=th, batch=b, pix_per_thread=ppt), db[key]["ms"]
     configs = configs or G.TILE_CONFIGS
-    timings = {}
+    timings, by_kernels = {}, {}
     for (tw, th, b, ppt) in configs:
         c = replace(cfg, tile_w=tw, tile_h=th, batch=b, pix_per_thread=ppt, views_preset=False)
-        timings[f"{tw}x{th}x{b}x{ppt}"] = round(time_config(c, params, views, reps=reps), 4)
+        kernels = (tw, th) + tuple((x.batch, x.pix_per_thread) for x in G.composite_cfgs(c, M, [v.cam for v in views]))
+        if kernels not in by_kernels:
+            by_kernels[kernels] = round(time_config(c, params, views, reps=reps), 4)
+        timings[f"{tw}x{th}x{b}x{ppt}"] = by_kernels[kernels]
     best = min(timings, key=timings.get)
     tw, th, b, ppt = (int(x) for x in best.split("x"))
     if use_cache:

@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include "gps_internal.h"
+#include "render_common.h"
 #include "binning.h"
 #include "launch.h"
 #include "prof.h"
@@ -257,6 +258,22 @@ gps_status gps_workspace_size(const gps_render_cfg* cfg, int32_t n_gaussians, co
     gps_status st = compute_layout(cfg, n_gaussians, cams, n_views, &L);
     if (st != GPS_OK) return st;
     *out_bytes = L.total;
+    return GPS_OK;
+}
+
+gps_status gps_render_composite_cfg(const gps_render_cfg* cfg, int32_t n_gaussians, const gps_camera* cams,
+                                    int32_t n_views, gps_render_cfg* out_fwd, gps_render_cfg* out_bwd)
+{
+    if (!out_fwd || !out_bwd) return GPS_ERR_INVALID_ARG;
+    WsLayout L;
+    gps_status st = compute_layout(cfg, n_gaussians, cams, n_views, &L);
+    if (st != GPS_OK) return st;
+    const CompositeShape f = fwd_shape(cfg, L.n_tiles, L.nvg), b = bwd_shape(cfg, L.n_tiles, L.nvg);
+    *out_fwd = *out_bwd = *cfg;
+    out_fwd->batch = f.batch;
+    out_fwd->pix_per_thread = f.pixels;
+    out_bwd->batch = b.batch;
+    out_bwd->pix_per_thread = b.pixels;
     return GPS_OK;
 }
 

@@ -483,22 +483,14 @@ static void launch_cbwd(const ViewTable* vt, const RParams& rp, const WsPtrs& w,
 bool dispatch_cbwd(const gps_render_cfg* cfg, const ViewTable* vt, const RParams& rp, const WsPtrs& w, int n_tiles,
                    int explicit_up, const float* loss_scale, hipStream_t s)
 {
-    if (one_pixel_per_lane(cfg, n_tiles, cfg->tile_w * cfg->tile_h == 256 ? kSmallGrid : kSmallGridBwd)) {
-        if (cfg->tile_w == 16 && cfg->tile_h == 16)
-            launch_cbwd<16, 16, 256, 1>(vt, rp, w, n_tiles, explicit_up, loss_scale, s);
-        else if (cfg->tile_w == 16 && cfg->tile_h == 32)
-            launch_cbwd<16, 32, 128, 1>(vt, rp, w, n_tiles, explicit_up, loss_scale, s);
-        else if (cfg->tile_w == 32 && cfg->tile_h == 16)
-            launch_cbwd<32, 16, 128, 1>(vt, rp, w, n_tiles, explicit_up, loss_scale, s);
-        else return false;
-        return true;
-    }
-#define X(tw, th, b, ppt)                                                                              \
-    if (cfg->tile_w == tw && cfg->tile_h == th && cfg->batch == b && cfg->pix_per_thread == ppt) {   \
-        launch_cbwd<tw, th, b, ppt>(vt, rp, w, n_tiles, explicit_up, loss_scale, s);                 \
-        return true;                                                                                 \
+    const CompositeShape c = bwd_shape(cfg, n_tiles, rp.nvg);
+#define X(tw, th, b, ppt)                                                                           \
+    if (cfg->tile_w == tw && cfg->tile_h == th && c.batch == b && c.pixels == ppt) {                \
+        launch_cbwd<tw, th, b, ppt>(vt, rp, w, n_tiles, explicit_up, loss_scale, s);                \
+        return true;                                                                                \
     }
     GPS_TILE_CONFIGS(X)
+    GPS_SMALL_BWD_CONFIGS(X)
 #undef X
     return false;
 }

@@ -307,20 +307,14 @@ static void launch_cfwd(const ViewTable* vt, const RParams& rp, const WsPtrs& w,
 bool dispatch_cfwd(const gps_render_cfg* cfg, const ViewTable* vt, const RParams& rp, const WsPtrs& w, int n_tiles,
                    hipStream_t s)
 {
-    if (one_pixel_per_lane(cfg, n_tiles, kSmallGrid)) {
-        // (batches of 256: fewer barriers; 128 for the 1280x720 view above 4 % slower)
-        if (cfg->tile_w == 16 && cfg->tile_h == 16) launch_cfwd<16, 16, 256, 1>(vt, rp, w, n_tiles, s);
-        else if (cfg->tile_w == 16 && cfg->tile_h == 32) launch_cfwd<16, 32, 256, 1>(vt, rp, w, n_tiles, s);
-        else if (cfg->tile_w == 32 && cfg->tile_h == 16) launch_cfwd<32, 16, 256, 1>(vt, rp, w, n_tiles, s);
-        else return false;
-        return true;
-    }
-#define X(tw, th, b, ppt)                                                                                  \
-    if (cfg->tile_w == tw && cfg->tile_h == th && cfg->batch == b && cfg->pix_per_thread == ppt) {       \
-        launch_cfwd<tw, th, b, ppt>(vt, rp, w, n_tiles, s);                                             \
-        return true;                                                                                     \
+    const CompositeShape c = fwd_shape(cfg, n_tiles, rp.nvg);
+#define X(tw, th, b, ppt)                                                                           \
+    if (cfg->tile_w == tw && cfg->tile_h == th && c.batch == b && c.pixels == ppt) {                \
+        launch_cfwd<tw, th, b, ppt>(vt, rp, w, n_tiles, s);                                         \
+        return true;                                                                                \
     }
     GPS_TILE_CONFIGS(X)
+    GPS_SMALL_FWD_CONFIGS(X)
 #undef X
     return false;
 }

@@ -198,23 +198,51 @@ __device__ __forceinline__ unsigned int wave_support_mask(const float4& r0, cons
     return mk;
 }
 
+// Records staged per batch and pixels per lane that the compositing kernels run with: what the
+// configuration asks, but for one pixel per lane on small grids.  There the longest list bounds the
+// compositing, and a wavefront walks it in fewer instructions the fewer pixels its lanes have; with many
+// short lists the batches' barriers and loads count, which fewer wavefronts share.  With n view-Gaussians a
+// wavefront (at one pixel a lane), forward / backward in us, two pixels and one, tiles of 16x32:
+//   1024x576 (9216 wavefronts)  n = 1.1: 18 / 27 and 22 / 26   3.3: 28 / 51 and 29 / 44    11: 79 / 125 and 59 / 113
+//   1280x720 (14720)            n = 2.0: 31 / 50 and 36 / 55   6.8: 76 / 130 and 70 / 140  20: 149 / 288 and 148 / 292
+//   1408x792 (17600)            n = 1.7: 35 / 54 and 40 / 63   5.7: 79 / 143 and 79 / 158  17: 159 / 299 and 153 / 309
+//   1536x864 (20736)            n = 1.4: 38 / 60 and 46 / 70   4.8: 80 / 158 and 90 / 178  14: 162 / 309 and 168 / 336
+//   640x480 (4800)              n = 2.1: 16 / 27 and 14 / 22   21: 96 / 160 and 63 / 129
+// and of 16x16:
+//   1024x576 (9216)             n = 1.1: 19 / 26 and 20 / 26   3.3: 29 / 48 and 25 / 45    11: 68 / 122 and 55 / 113
+//   1280x720 (14400)            n = 0.7: 25 / 32 and 26 / 34   2.1: 33 / 60 and 31 / 58    6.9: 66 / 152 and 61 / 141
+//   1536x864 (20736)            n = 0.5: 32 / 40 and 31 / 44   1.4: 39 / 73 and 39 / 73    4.8: 81 / 190 and 78 / 184
+// (Beyond 16384 wavefronts one pixel is better for 1 M Gaussians alone, and for tiles of 256 pixels by 5 %.)
+struct CompositeShape {
+    int batch, pixels;
+};
+constexpr long long kFewestWaves = 5120;                         // below: one pixel whatever the lists
+constexpr long long kSmallGrid = 16384, kSmallGridBwd = 10240;  // (the latter for tiles of 512 pixels)
+constexpr long long kListFwd = 3, kListBwd = 1;                  // least view-Gaussians a wavefront between
+
+inline bool one_pixel_per_lane(const gps_render_cfg* cfg, int n_tiles, long long nvg, long long limit, long long list)
+{
+    const long long waves = (long long)n_tiles * cfg->tile_w * cfg->tile_h / 64;
+    return cfg->pix_per_thread > 1 && (waves <= kFewestWaves || (waves <= limit && nvg >= list * waves));
+}
+
+// (Batches of 256 in the forward: fewer barriers; 128 takes 4 % longer for a 1280x720 view of 100 k.)
+inline CompositeShape fwd_shape(const gps_render_cfg* cfg, int n_tiles, long long nvg)
+{
+    if (one_pixel_per_lane(cfg, n_tiles, nvg, kSmallGrid, kListFwd)) return {256, 1};
+    return {cfg->batch, cfg->pix_per_thread};
+}
+
+inline CompositeShape bwd_shape(const gps_render_cfg* cfg, int n_tiles, long long nvg)
+{
+    const bool small = cfg->tile_w * cfg->tile_h == 256;
+    if (one_pixel_per_lane(cfg, n_tiles, nvg, small ? kSmallGrid : kSmallGridBwd, kListBwd)) return {small ? 256 : 128, 1};
+    return {cfg->batch, cfg->pix_per_thread};
+}
+
 // Tile configurations (tile width, height, staged batch, pixels per lane) for
 // which both compositing kernels are instantiated.  A 32-pixel-wide tile reads
 // each row of a float image plane as one whole 128-byte line.
-// Small grids take one pixel per lane whatever the configuration asks: below 10 to 16 wavefronts
-// a SIMD (at one pixel a lane) what bounds the compositing is the longest list, which a
-// wavefront walks in fewer instructions the fewer pixels its lanes have.  Forward / backward in
-// us with two pixels and with one, 100 k Gaussians, tiles of 16x32: 640x480 105 / 178 and 68 / 140,
-// 1120x630 (11200 wavefronts) 82 / 135 and 65 / 132 (32x16: 96 / 152 and 65 / 156), 1280x720 (14720)
-// 81 / 139 and 74 / 152, 1600x900 (23200) 88 / 174 and 104 / 200; of 16x16: 1280x720 (14400)
-// 72 / 164 and 65 / 155, 1600x900 (22800) 88 / 214 and 87 / 210.
-constexpr long long kSmallGrid = 16384, kSmallGridBwd = 10240;  // (the latter for tiles of 512 pixels)
-
-inline bool one_pixel_per_lane(const gps_render_cfg* cfg, int n_tiles, long long few_waves)
-{
-    return cfg->pix_per_thread > 1 && (long long)n_tiles * cfg->tile_w * cfg->tile_h / 64 <= few_waves;
-}
-
 #define GPS_TILE_CONFIGS(X) \
     X(8, 8, 128, 1)         \
     X(8, 8, 256, 1)         \
@@ -235,5 +263,10 @@ inline bool one_pixel_per_lane(const gps_render_cfg* cfg, int n_tiles, long long
     X(16, 32, 512, 4)       \
     X(32, 16, 128, 2)       \
     X(32, 16, 256, 2)
+// and those of small grids alone
+#define GPS_SMALL_FWD_CONFIGS(X) \
+    X(16, 32, 256, 1)            \
+    X(32, 16, 256, 1)
+#define GPS_SMALL_BWD_CONFIGS(X) X(32, 16, 128, 1)
 
 }  // namespace gps

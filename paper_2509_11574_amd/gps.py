@@ -10,7 +10,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 
 import numpy as np
 import torch
@@ -113,7 +113,7 @@ EXPORTS = ["gps_abi_version", "gps_status_string", "gps_render_cfg_default", "gp
            "gps_insert_gaussians", "gps_depth_downsample", "gps_icp_workspace_size", "gps_icp_reduce",
            "gps_icp_solve", "gps_render_bwd_adam", "gps_level_camera", "gps_icp_reduce_noalloc",
            "gps_hash_reset", "gps_hash_fuse", "gps_hash_raycast", "gps_stream_blocks", "gps_stream_read",
-           "gps_stream_write", "gps_icp_step"]
+           "gps_stream_write", "gps_icp_step", "gps_render_composite_cfg"]
 
 _lib = None
 
@@ -136,6 +136,7 @@ def lib():
         L.gps_render_cfg_default.argtypes = [P]
         L.gps_render_cfg_default.restype = None
         L.gps_workspace_size.argtypes = [P, I32, P, I32, ctypes.POINTER(ctypes.c_size_t)]
+        L.gps_render_composite_cfg.argtypes = [P, I32, P, I32, P, P]
         L.gps_workspace_reset.argtypes = [P, ctypes.c_size_t, P]
         L.gps_fuse.argtypes = [P, P, P, P, P]
         L.gps_raycast.argtypes = [P, P, I32, P, P, F, F, P]
@@ -549,6 +550,16 @@ def workspace_size(cfg: RenderCfg, n_gaussians: int, cams) -> int:
     _check(lib().gps_workspace_size(ctypes.byref(cs), int(n_gaussians), carr, len(cams), ctypes.byref(out)),
            "gps_workspace_size")
     return out.value
+
+
+def composite_cfgs(cfg: RenderCfg, n_gaussians: int, cams):
+    """The configurations that the compositing forward and backward run with (gps_render_composite_cfg): cfg,
+    but for one pixel per lane, and a batch of its own, on small grids where cfg asks for more."""
+    cams = [camera(c) for c in cams]
+    cs, f, b = cfg.struct(), RenderCfgS(), RenderCfgS()
+    _check(lib().gps_render_composite_cfg(ctypes.byref(cs), int(n_gaussians), (Camera * len(cams))(*cams), len(cams),
+                                          ctypes.byref(f), ctypes.byref(b)), "gps_render_composite_cfg")
+    return tuple(replace(cfg, batch=x.batch, pix_per_thread=x.pix_per_thread) for x in (f, b))
 
 
 class Workspace:
