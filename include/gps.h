@@ -333,6 +333,10 @@ gps_status gps_hash_fuse(const gps_hash_volume* vol, const gps_camera* cam, cons
 #define GPS_HASH_TILE 16
 #define GPS_HASH_RANGE_FLOATS(width, height) \
     (2 * (((width) + GPS_HASH_TILE - 1) / GPS_HASH_TILE) * (((height) + GPS_HASH_TILE - 1) / GPS_HASH_TILE))
+/* The scratch floats that gps_hash_raycast of these views puts to use: GPS_HASH_RANGE_FLOATS over the
+ * views, or 0 where it marches with the directory. */
+gps_status gps_hash_range_floats(const gps_hash_volume* vol, const gps_camera* cams, int32_t n_views,
+                                 size_t* out_floats);
 gps_status gps_hash_raycast(const gps_hash_volume* vol, const gps_camera* cams, int32_t n_views,
                             float* const* out_depth, float* const* out_rgb, float z_near, float step, float* range,
                             size_t range_floats, void* stream);

@@ -357,6 +357,17 @@ gps_status gps_hash_fuse(const gps_hash_volume* vol, const gps_camera* cam, cons
     return launch_hash_fuse(vol, cam, depth, rgb, (hipStream_t)stream);
 }
 
+gps_status gps_hash_range_floats(const gps_hash_volume* vol, const gps_camera* cams, int32_t n_views, size_t* out_floats)
+{
+    gps_status st = hash_vol_ok(vol);
+    if (st != GPS_OK) return st;
+    if (!cams || !out_floats || n_views < 1 || n_views > GPS_MAX_VIEWS) return GPS_ERR_INVALID_ARG;
+    for (int v = 0; v < n_views; ++v)
+        if (!cam_ok(cams[v])) return GPS_ERR_INVALID_ARG;
+    *out_floats = hash_raycast_ranges(vol, cams, n_views) ? hash_range_floats(cams, n_views) : 0;
+    return GPS_OK;
+}
+
 gps_status gps_hash_raycast(const gps_hash_volume* vol, const gps_camera* cams, int32_t n_views,
                             float* const* out_depth, float* const* out_rgb, float z_near, float step, float* range,
                             size_t range_floats, void* stream)

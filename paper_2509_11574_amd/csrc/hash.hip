@@ -737,12 +737,14 @@ gps_status launch_hash_fuse(const gps_hash_volume* v, const gps_camera* cam, con
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 
-// The directory's shape, and whether the region and the pool fit it.
-static bool hash_dir_shape(const HashDev& h, HashDirShape* sh)
+// The directory's shape and the views' 8x8-pixel tiles, and whether the region, the pool and the tiles fit it.
+static bool hash_dir_shape(const HashDev& h, const gps_camera* cams, int n_views, HashDirShape* sh, long long* tiles)
 {
+    *tiles = 0;
+    for (int k = 0; k < n_views; ++k) *tiles += (long long)((cams[k].width + 7) / 8) * ((cams[k].height + 7) / 8);
     const long long blocks = (long long)h.nb[0] * h.nb[1] * h.nb[2];
     const long long wx = (h.nb[0] + 31) / 32, words = wx * h.nb[1] * h.nb[2];
-    if (blocks > kDirBlocks || words > kDirWords || h.cap > (int)kDirNone) return false;
+    if (blocks > kDirBlocks || words > kDirWords || h.cap > (int)kDirNone || *tiles >= (1ll << 31) - (1 << 20)) return false;
     for (int k = 0; k < 3; ++k) sh->nb[k] = h.nb[k];
     sh->wx = (int)wx;
     sh->sn1 = (h.nb[1] + 3) / 4;
@@ -760,6 +762,13 @@ size_t hash_range_floats(const gps_camera* cams, int n_views)
     return n;
 }
 
+bool hash_raycast_ranges(const gps_hash_volume* v, const gps_camera* cams, int n_views)
+{
+    HashDirShape sh;
+    long long tiles;
+    return !hash_dir_shape(hash_dev(*v), cams, n_views, &sh, &tiles);
+}
+
 gps_status launch_hash_raycast(const gps_hash_volume* v, const gps_camera* cams, int n_views,
                                float* const* out_depth, float* const* out_rgb, float z_near, float step, float* range,
                                hipStream_t s)
@@ -772,15 +781,12 @@ gps_status launch_hash_raycast(const gps_hash_volume* v, const gps_camera* cams,
     const int bgrid = v->capacity < kHashGrid ? v->capacity : kHashGrid;
     if (v->block_min) GPS_LAUNCH(K_BRICK_MIN, s, k_hash_block_min, dim3((bgrid + 3) / 4), dim3(256), 0, s, h);
     HashDirShape sh;
-    if (hash_dir_shape(h, &sh)) {
-        long long tiles = 0;
-        for (int k = 0; k < n_views; ++k) tiles += (long long)((cams[k].width + 7) / 8) * ((cams[k].height + 7) / 8);
-        if (tiles < (1ll << 31) - (1 << 20)) {
-            const size_t bytes = 4 * (size_t)(sh.dir_words + 2 * sh.plane_words + sh.sup_words);
-            const int groups = tiles < 512 ? (int)tiles : 512;  // two a compute unit
-            GPS_LAUNCH(K_RAYCAST, s, k_hash_raycast_dir, dim3(groups), dim3(kDirThreads), bytes, s, a, h, sh, (int)tiles);
-            return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
-        }
+    long long dir_tiles;
+    if (hash_dir_shape(h, cams, n_views, &sh, &dir_tiles)) {
+        const size_t bytes = 4 * (size_t)(sh.dir_words + 2 * sh.plane_words + sh.sup_words);
+        const int groups = dir_tiles < 512 ? (int)dir_tiles : 512;  // two a compute unit
+        GPS_LAUNCH(K_RAYCAST, s, k_hash_raycast_dir, dim3(groups), dim3(kDirThreads), bytes, s, a, h, sh, (int)dir_tiles);
+        return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
     }
     HashRange hr;
     hr.range = nullptr;

@@ -113,7 +113,7 @@ EXPORTS = ["gps_abi_version", "gps_status_string", "gps_render_cfg_default", "gp
            "gps_insert_gaussians", "gps_depth_downsample", "gps_icp_workspace_size", "gps_icp_reduce",
            "gps_icp_solve", "gps_render_bwd_adam", "gps_level_camera", "gps_icp_reduce_noalloc",
            "gps_hash_reset", "gps_hash_fuse", "gps_hash_raycast", "gps_stream_blocks", "gps_stream_read",
-           "gps_stream_write", "gps_icp_step", "gps_render_composite_cfg"]
+           "gps_stream_write", "gps_icp_step", "gps_render_composite_cfg", "gps_hash_range_floats"]
 
 _lib = None
 
@@ -168,6 +168,7 @@ def lib():
         L.gps_stream_write.argtypes = [P, ctypes.c_size_t, F, P]
         L.gps_hash_fuse.argtypes = [P, P, P, P, P]
         L.gps_hash_raycast.argtypes = [P, P, I32, P, P, F, F, P, ctypes.c_size_t, P]
+        L.gps_hash_range_floats.argtypes = [P, P, I32, ctypes.POINTER(ctypes.c_size_t)]
         L.gps_icp_solve.argtypes = [P, P, P, P]
         L.gps_render_bwd_adam.argtypes = [P, P, P, I32, P, P, P, P, P, P, P, ctypes.c_size_t, P]
         L.gps_level_camera.argtypes = [P, I32, P]
@@ -447,7 +448,7 @@ def hash_range_floats(cams) -> int:
 
 def hash_raycast(vol: HashVolume, cams, z_near=0.2, step=0.0, out=None, stream=None, range_scratch=True):
     """As raycast, over the hashed volume.  range_scratch: True (a scratch tensor is
-    allocated here), a float32 device tensor of at least hash_range_floats(cams)
+    allocated here where the march uses one), a float32 device tensor of at least hash_range_floats(cams)
     elements, or None/False (the rays march the whole region)."""
     cams = [camera(c) for c in cams]
     V = len(cams)
@@ -460,7 +461,10 @@ def hash_raycast(vol: HashVolume, cams, z_near=0.2, step=0.0, out=None, stream=N
     s = vol.struct()
     rng = None
     if range_scratch is True:
-        rng = torch.empty(hash_range_floats(cams), dtype=torch.float32, device=vol.tsdf.device)
+        n = ctypes.c_size_t(0)
+        _check(lib().gps_hash_range_floats(ctypes.byref(s), carr, V, ctypes.byref(n)), "gps_hash_range_floats")
+        if n.value > 0:
+            rng = torch.empty(n.value, dtype=torch.float32, device=vol.tsdf.device)
     elif range_scratch is not None and range_scratch is not False:
         rng = range_scratch
     _check(lib().gps_hash_raycast(ctypes.byref(s), carr, V, dptr, cptr, float(z_near), float(step),
