@@ -37,6 +37,7 @@ struct FuseArgs {
     unsigned int N;
     int lx;                     // log2 of a cell's width
     unsigned int cx, cy, cells;  // cells along x, along y, in all
+    unsigned int first;         // of this launch
     float* tsdf;
     float* w;
     float* col;
@@ -88,7 +89,7 @@ __global__ void __launch_bounds__(64 * kFuseWaves) k_fuse(FuseArgs a)
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int wx = 1 << a.lx, wy = 64 >> a.lx;
     if (wid == 0) {
-        const unsigned int c = lane * gridDim.x + blockIdx.x, r = c / a.cx;
+        const unsigned int c = a.first + lane * gridDim.x + blockIdx.x, r = c / a.cx;
         const int x0 = (int)(c - r * a.cx) << a.lx, z = (int)(r / a.cy);
         const int y0 = (int)(r - (unsigned int)z * a.cy) * wy;
         const bool seen = c < a.cells && !fuse_outside(a.ctx, x0, min(x0 + wx, a.nx) - 1, y0, min(y0 + wy, a.ny) - 1, z);
@@ -136,8 +137,13 @@ gps_status launch_fuse(const gps_volume* vol, const gps_camera* cam, const float
     a.cx = (unsigned int)((a.nx + (1 << a.lx) - 1) >> a.lx);
     a.cy = (unsigned int)((a.ny + (64 >> a.lx) - 1) / (64 >> a.lx));
     a.cells = a.cx * a.cy * (unsigned int)vol->nz;
-    const unsigned int blocks = (a.cells + 63u) / 64u;
-    GPS_LAUNCH(K_FUSE, s, k_fuse, dim3(blocks), dim3(64 * kFuseWaves), 0, s, a);
+    // 2^31 lanes a launch (a launch may have up to 2^32 - 1; a lattice 2 points wide and high
+    // has a cell for every 4 points)
+    constexpr unsigned int kLaunchCells = 64u << 22;
+    for (a.first = 0u; a.first < a.cells; a.first += kLaunchCells) {
+        const unsigned int n = std::min(a.cells - a.first, kLaunchCells);
+        GPS_LAUNCH(K_FUSE, s, k_fuse, dim3((n + 63u) / 64u), dim3(64 * kFuseWaves), 0, s, a);
+    }
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
 
