@@ -44,9 +44,10 @@ constexpr int kRunFew = 8, kRunShort = 16, kRunLong = 64, kRunIters = 4;
 // Gaussians, so they decide the last bits of the images and, where a residual is within those bits of zero,
 // the sign of its L1 adjoint.  The order is this: group k of 64 consecutive view-Gaussians (numbered
 // over the views) takes its places in part k mod 4 of each tile's range, in each part as the
-// groups arrive.  So the blocks are single wavefronts over such groups (the ones in flight together a
-// multiple of kCntSplit), and kCntSplit shared rows the parts.  With LDS rows over the whole map a pass over
-// 70 k Gaussians at 953x617 takes 157 us, not 163, and each pixel adds in another order.
+// groups arrive.  So the blocks take such groups (the ones in flight together a multiple of kCntSplit), and
+// kCntSplit shared rows are the parts.  A pass over 70 k Gaussians at 953x617 takes 160 us, over two views of
+// 901x675 and 161x120 and 42 k 213; with the walk by one wavefront a group 163 and 221; with LDS rows
+// over the whole map, and so another order, 157 and 202.
 constexpr int kOrderGroup = 64;
 
 inline BinShape bin_shape(int M, int V, size_t n_tiles, size_t most_tiles, unsigned long long cap,
@@ -60,7 +61,7 @@ inline BinShape bin_shape(int M, int V, size_t n_tiles, size_t most_tiles, unsig
         const int most = std::max(kMostWaves / V / kCntSplit, 1) * kCntSplit;
         b.unsorted = 1;
         b.waves = 1;
-        b.per = b.run = kOrderGroup;
+        b.per = kOrderGroup;
         b.rows = kCntSplit;
         b.iters = (wanted + most - 1) / most;
         b.chunks = ((wanted + b.iters - 1) / b.iters + kCntSplit - 1) / kCntSplit * kCntSplit;

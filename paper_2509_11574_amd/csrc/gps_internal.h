@@ -97,8 +97,8 @@ struct WsHeader {
 // wavefronts per view, a wavefront taking `per` Gaussians `iters` times, as runs of `run`
 // consecutive ones (see binning.h).  With `lds` a block counts its instances per tile in LDS
 // (`lds_words` counters) and has a row of tile counts of its own (rows = chunks); otherwise
-// the blocks of a view share `rows` rows in memory.  With `unsorted` the share of a block is a
-// group of kOrderGroup consecutive view-Gaussians at a time.
+// the blocks of a view share `rows` rows in memory.  With `unsorted` a block takes a group of
+// kOrderGroup consecutive view-Gaussians `iters` times, and numbers its slots as one (waves = 1).
 struct BinShape {
     int chunks, waves, per, iters, run, rows, lds, lds_words, unsorted;
 };

@@ -12,6 +12,7 @@
 //   k_scan_rows    per tile: each block's first place; one block: the slots' numbers
 //   k_scan_tiles   one block: tile ranges (k_scan_small: both in one launch, where they are few)
 //   k_emit         (depth, view-Gaussian) keys scattered into tile ranges
+//                  (k_project_groups, k_emit_groups: the same where no sort follows)
 //   k_tile_sort_large  per tile of >= kLongTile instances: its keys by depth buckets in LDS
 //                  (shorter lists: registers of the compositing block's first wavefront)
 //   k_composite_fwd<TW,TH,B,PPT>  (composite_fwd.hip) per tile: LDS-staged
@@ -172,31 +173,17 @@ __device__ __forceinline__ unsigned int lanes_before(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
 }
 
-// The Gaussian of a lane in iteration i of a wavefront's share (M: none).  skew: of the first group, those of
-// the view before.
+// The Gaussian of a lane in iteration i of a wavefront's share (M: none).
 template <int PER>
-__device__ __forceinline__ int share_gaussian(const BinShape& bs, int chunk, int wid, int lane, int i, int M,
-                                              unsigned int skew)
+__device__ __forceinline__ int share_gaussian(const BinShape& bs, int chunk, int wid, int lane, int i, int M)
 {
     if (lane >= PER) return M;
     const unsigned int per = (unsigned int)(PER / bs.run);  // runs a wavefront takes at a time
     const unsigned long long waves = (unsigned long long)bs.chunks * bs.waves;
     const unsigned long long r = ((unsigned long long)i * per + (unsigned int)(lane / bs.run)) * waves +
                                  (unsigned int)(chunk * bs.waves + wid);
-    const unsigned long long g = r * bs.run + (unsigned int)(lane % bs.run) - skew;  // (below 0: beyond M)
+    const unsigned long long g = r * bs.run + (unsigned int)(lane % bs.run);
     return g < (unsigned long long)M ? (int)g : M;
-}
-
-// Where the shared rows are the parts of an unsorted list: the place of view v's first Gaussian in its
-// group, and the row of a block.
-__device__ __forceinline__ unsigned int group_skew(const BinShape& bs, int v, int M)
-{
-    return bs.unsorted ? (unsigned int)(v * M) % kOrderGroup : 0u;
-}
-
-__device__ __forceinline__ int shared_row(const BinShape& bs, int v, int chunk, int M)
-{
-    return (bs.unsorted ? chunk + v * M / kOrderGroup : chunk) % bs.rows;
 }
 
 // The slots of the window [w0, w0 + 64) of a walk: for this lane's slot its owner in the
@@ -259,6 +246,30 @@ __device__ __forceinline__ bool slot_passes(const SupportTest& st, float z, int 
            z < tile_max + rp.eps;
 }
 
+// Projection of Gaussian g, and what is kept of it: its record, first tile, depth and the tiles of its
+// rectangle (span, also of one that is not seen).  Returns its slots: one per covered tile.
+template <bool SH>
+__device__ __forceinline__ unsigned int project_store(const DevView& V, const RParams& rp, const GParams& gp, const WsPtrs& w,
+                                                      int g, size_t vg, ProjOut& p, unsigned int& t0, unsigned int& span)
+{
+    unsigned int n = 0u;
+    p = project_one<SH>(V, rp, gp, g);
+    TileRect r;
+    if (p.valid && rect_of(p.r0.x, p.r0.y, p.r2.z, p.r2.w, V.cam.W, V.cam.H, rp.tile_w, rp.tile_h, &r)) {
+        const unsigned int width = (unsigned int)(r.tx1 - r.tx0 + 1), height = (unsigned int)(r.ty1 - r.ty0 + 1);
+        n = width * height;
+        span = width | height << 16;
+        t0 = (unsigned int)r.tx0 | (unsigned int)r.ty0 << 16;
+        w.rec[3 * vg + 0] = p.r0;
+        w.rec[3 * vg + 1] = p.r1;
+        w.rec[3 * vg + 2] = p.r2;
+        w.off[vg] = t0;
+        w.depth[vg] = p.r1.z;
+    }
+    w.span[vg] = span;
+    return n;
+}
+
 // ---------------------------------------------------------------- project
 // Projection of a share of one view's Gaussians (see binning.h), the number of slots of
 // each (tiles of its rectangle), and the walk that counts the instances per tile: those that
@@ -275,9 +286,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_project(const ViewTable* __re
     const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
     const DevView& V = vt.v[v];
     const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const unsigned int skew = LDS ? 0u : group_skew(bs, v, rp.M);
-    unsigned int* row =
-        w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : shared_row(bs, v, chunk, rp.M)) * n_tiles;
+    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
     CountWalk<PER>& ww = walk[wid];
     const float l2amin = __log2f(rp.amin);
     if (LDS) {
@@ -286,25 +295,12 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_project(const ViewTable* __re
     }
     unsigned long long slots = 0ull;
     for (int i = 0; i < bs.iters; ++i) {
-        const int g = share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew);
+        const int g = share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
         const size_t vg = (size_t)v * rp.M + g;
         unsigned int n = 0u, t0 = 0u, span = 0u, kept = 0u;
         ProjOut p;
         if (g < rp.M) {
-            p = project_one<SH>(V, rp, gp, g);
-            TileRect r;
-            if (p.valid && rect_of(p.r0.x, p.r0.y, p.r2.z, p.r2.w, V.cam.W, V.cam.H, rp.tile_w, rp.tile_h, &r)) {
-                const unsigned int width = (unsigned int)(r.tx1 - r.tx0 + 1), height = (unsigned int)(r.ty1 - r.ty0 + 1);
-                n = width * height;  // one slot per covered tile
-                span = width | height << 16;
-                t0 = (unsigned int)r.tx0 | (unsigned int)r.ty0 << 16;
-                w.rec[3 * vg + 0] = p.r0;
-                w.rec[3 * vg + 1] = p.r1;
-                w.rec[3 * vg + 2] = p.r2;
-                w.off[vg] = t0;
-                w.depth[vg] = p.r1.z;
-            }
-            w.span[vg] = span;
+            n = project_store<SH>(V, rp, gp, w, g, vg, p, t0, span);
         }
         const unsigned int excl = wave_incl_sum(n) - n;
         const unsigned int total = (unsigned int)__builtin_amdgcn_readlane((int)(excl + n), 63);
@@ -616,16 +612,14 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
     const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
     const DevView& V = vt.v[v];
     const int n_tiles = V.tiles_x * V.tiles_y, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const unsigned int skew = LDS ? 0u : group_skew(bs, v, rp.M);
-    unsigned int* row =
-        w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : shared_row(bs, v, chunk, rp.M)) * n_tiles;
+    unsigned int* row = w.tile_rows + (size_t)bs.rows * V.tile_base + (size_t)(LDS ? chunk : chunk % bs.rows) * n_tiles;
     const unsigned int* start = w.tile_start + V.tile_base;
     EmitWalk<PER>& ww = walk[wid];
     // A Gaussian's loads are issued an iteration ahead.
     unsigned int span = 0u, t0 = 0u, kept = 0u, span1 = 0u, t01 = 0u, kept1 = 0u;
     float z = 0.0f, z1 = 0.0f;
     auto load = [&](int i) {
-        const int g = i < bs.iters ? share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew) : rp.M;
+        const int g = i < bs.iters ? share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M) : rp.M;
         span1 = 0u;
         if (g < rp.M) {
             const size_t vg = (size_t)v * rp.M + g;
@@ -644,7 +638,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
     }
     const float l2amin = __log2f(rp.amin);
     for (int i = 0; i < bs.iters; ++i) {
-        const size_t vg = (size_t)v * rp.M + share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M, skew);
+        const size_t vg = (size_t)v * rp.M + share_gaussian<PER>(bs, chunk, wid, lane, i, rp.M);
         span = span1;
         t0 = t01;
         kept = kept1;
@@ -669,7 +663,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
                 const uint4 c = ww.c[owner];
                 int tx, ty;
                 const Slot s = slot_of<LDS>(c, w0 + lane, V.tiles_x, &tx, &ty);
-                const int owner_g = share_gaussian<PER>(bs, chunk, wid, (c.w >> 16) & 63, i, rp.M, skew);
+                const int owner_g = share_gaussian<PER>(bs, chunk, wid, (c.w >> 16) & 63, i, rp.M);
                 bool pass;
                 if (s.small) {
                     pass = (ww.kept[owner] >> s.j) & 1u;
@@ -691,6 +685,173 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_emit(const ViewTable* __restr
                 }
             }
         }
+        base += total;
+    }
+}
+
+// ------------------------------------------------------- lists without a sort
+// Projection and emission where no sort follows (see kOrderGroup): a block takes groups of 64 consecutive
+// view-Gaussians, numbered over the views, its first wavefront a lane each, and all its lanes then walk the
+// concatenation of their tile rectangles, 256 slots at a time; group k adds to shared row k mod
+// kCntSplit, which is its part of a tile's range.
+struct GroupWalk {
+    uint4 c[kOrderGroup];  // as in WaveWalk
+    unsigned int kept[kOrderGroup];
+    unsigned int seen, total;
+};
+
+// The view-Gaussian of a lane of the block's i-th group in its view (M: none).
+__device__ __forceinline__ int group_gaussian(const BinShape& bs, int v, int chunk, int lane, int i, int M)
+{
+    const unsigned int g = ((unsigned int)i * bs.chunks + chunk) * kOrderGroup + lane;
+    const unsigned int skew = (unsigned int)(v * M) % kOrderGroup;  // of the view's first group, those of the view before
+    return g >= skew && g - skew < (unsigned int)M ? (int)(g - skew) : M;
+}
+
+__device__ __forceinline__ unsigned int* group_row(const BinShape& bs, const DevView& V, const WsPtrs& w, int v, int chunk, int M)
+{
+    const int part = (chunk + v * M / kOrderGroup) % kCntSplit;  // (chunks is a multiple of kCntSplit)
+    return w.tile_rows + (size_t)kCntSplit * V.tile_base + (size_t)part * V.tiles_x * V.tiles_y;
+}
+
+// The Gaussian in the block's list that slot i belongs to: the last that starts at or before it.
+__device__ __forceinline__ unsigned int group_owner(const GroupWalk& gw, unsigned int i)
+{
+    unsigned int lo = 0u, hi = gw.seen;
+#pragma unroll
+    for (int step = 0; step < 6; ++step) {
+        const unsigned int mid = (lo + hi) >> 1;
+        if (gw.c[mid].y <= i) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+template <bool SH>
+__global__ void __launch_bounds__(kBlk) k_project_groups(const ViewTable* __restrict__ vtp, RParams rp, BinShape bs,
+                                                         GParams gp, WsPtrs w)
+{
+    __shared__ GroupWalk gw;
+    __shared__ float4 sa[kOrderGroup], sb[kOrderGroup];  // the support tests, as in CountWalk
+    const ViewTable& vt = *vtp;
+    const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
+    const DevView& V = vt.v[v];
+    const int lane = threadIdx.x & 63;
+    const bool first = threadIdx.x < 64;
+    unsigned int* row = group_row(bs, V, w, v, chunk, rp.M);
+    const float l2amin = __log2f(rp.amin);
+    unsigned long long slots = 0ull;
+    for (int i = 0; i < bs.iters; ++i) {
+        unsigned int n = 0u, at = 0u;
+        size_t vg = 0;
+        if (first) {
+            const int g = group_gaussian(bs, v, chunk, lane, i, rp.M);
+            vg = (size_t)v * rp.M + g;
+            unsigned int t0 = 0u, span = 0u;
+            ProjOut p;
+            if (g < rp.M) n = project_store<SH>(V, rp, gp, w, g, vg, p, t0, span);
+            const unsigned int excl = wave_incl_sum(n) - n;
+            const unsigned long long seen = __builtin_amdgcn_ballot_w64(n > 0u);
+            at = lanes_before(seen);
+            if (n > 0u) {
+                const SupportTest st(p.r0, p.r1, l2amin);
+                sa[at] = make_float4(st.mx, st.my, st.A, st.B);
+                sb[at] = make_float4(st.C, st.kx, st.ky, st.need);
+                gw.c[at] = make_uint4(__float_as_uint(p.r1.z), excl, t0,
+                                      (span & 0xffffu) | (n > (unsigned int)kKeptBits ? 0x80000000u : 0u));
+                gw.kept[at] = 0u;
+            }
+            if (lane == 63) {
+                gw.seen = (unsigned int)__builtin_popcountll(seen);
+                gw.total = excl + n;
+            }
+        }
+        __syncthreads();
+        const unsigned int total = gw.total;
+        slots += total;
+        if (slots <= rp.cap) {  // else nothing of this forward is used
+            for (unsigned int k = threadIdx.x; k < total; k += kBlk) {
+                const unsigned int owner = group_owner(gw, k);
+                const uint4 c = gw.c[owner];
+                int tx, ty;
+                const Slot s = slot_of<false>(c, k, V.tiles_x, &tx, &ty);
+                if (slot_passes(SupportTest(sa[owner], sb[owner]), __uint_as_float(c.x), tx, ty,
+                                w.tilemax[V.tile_base + s.tile], rp)) {
+                    atomicAdd(row + s.tile, 1u);
+                    if (s.small) atomicOr(&gw.kept[owner], 1u << s.j);
+                }
+            }
+        }
+        __syncthreads();
+        if (n > 0u) w.kept[vg] = gw.kept[at];
+    }
+    if (threadIdx.x == 0) w.seg_sum[blockIdx.x] = (unsigned int)min(slots, 0xffffffffull);
+}
+
+__global__ void __launch_bounds__(kBlk) k_emit_groups(const ViewTable* __restrict__ vtp, RParams rp, BinShape bs, WsPtrs w)
+{
+    __shared__ GroupWalk gw;
+    const ViewTable& vt = *vtp;
+    const int v = blockIdx.x / bs.chunks, chunk = blockIdx.x - v * bs.chunks;
+    const DevView& V = vt.v[v];
+    const int lane = threadIdx.x & 63;
+    unsigned int* row = group_row(bs, V, w, v, chunk, rp.M);
+    const unsigned int* start = w.tile_start + V.tile_base;
+    const float l2amin = __log2f(rp.amin);
+    unsigned int base = w.seg_off[blockIdx.x];
+    const unsigned long long n_inst = w.hdr->n_inst;
+    for (int i = 0; i < bs.iters; ++i) {
+        if (threadIdx.x < 64) {
+            const int g = group_gaussian(bs, v, chunk, lane, i, rp.M);
+            const size_t vg = (size_t)v * rp.M + g;
+            unsigned int span = 0u, t0 = 0u, kept = 0u;
+            float z = 0.0f;
+            if (g < rp.M) {
+                span = w.span[vg];
+                t0 = w.off[vg];
+                kept = w.kept[vg];
+                z = w.depth[vg];
+            }
+            if (n_inst > rp.cap) span = 0u;
+            const unsigned int n = (span & 0xffffu) * (span >> 16);
+            const unsigned int excl = wave_incl_sum(n) - n;
+            const unsigned long long seen = __builtin_amdgcn_ballot_w64(n > 0u);
+            const unsigned int at = lanes_before(seen);
+            if (n > 0u) {
+                w.off[vg] = base + excl;
+                gw.c[at] = make_uint4(__float_as_uint(z), excl, t0,
+                                      (span & 0xffffu) | (unsigned int)lane << 16 | (n > (unsigned int)kKeptBits ? 0x80000000u : 0u));
+                gw.kept[at] = kept;
+            }
+            if (lane == 63) {
+                gw.seen = (unsigned int)__builtin_popcountll(seen);
+                gw.total = excl + n;
+            }
+        }
+        __syncthreads();
+        const unsigned int total = gw.total;
+        for (unsigned int k = threadIdx.x; k < total; k += kBlk) {
+            const unsigned int owner = group_owner(gw, k);
+            const uint4 c = gw.c[owner];
+            int tx, ty;
+            const Slot s = slot_of<false>(c, k, V.tiles_x, &tx, &ty);
+            const size_t vg = (size_t)v * rp.M + group_gaussian(bs, v, chunk, (c.w >> 16) & 63, i, rp.M);
+            bool pass = (gw.kept[owner] >> (s.j & 31u)) & 1u;
+            if (!s.small) {
+                const float4* r = w.rec + 3 * vg;
+                pass = slot_passes(SupportTest(r[0], r[1], l2amin), __uint_as_float(c.x), tx, ty, w.tilemax[V.tile_base + s.tile], rp);
+                if (!pass) {
+                    float* pz = w.partial + (size_t)(base + k) * kAdj;
+#pragma unroll
+                    for (int q = 0; q < kAdj; ++q) pz[q] = 0.0f;
+                }
+            }
+            if (pass) {
+                const unsigned int pos = start[s.tile] + atomicAdd(row + s.tile, 1u);
+                if (pos < rp.cap) w.keys[pos] = ((unsigned long long)c.x << 32) | (unsigned int)vg;
+            }
+        }
+        __syncthreads();
         base += total;
     }
 }
@@ -1192,8 +1353,11 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
             GPS_LAUNCH(K_SCAN, s, k_zero_rows, dim3((unsigned int)std::min((n + kBlk - 1) / kBlk, (size_t)1024)),
                        dim3(kBlk), 0, s, w, n);
         }
-        if (bs.unsorted) launch_project<1, kOrderGroup, false>(dvt, rp, bs, gp, w, s);
-        else if (bs.per == kFewPer && bs.lds) launch_project<kFewWaves, kFewPer, true>(dvt, rp, bs, gp, w, s);
+        if (bs.unsorted) {
+            const dim3 grid((unsigned int)(bs.chunks * rp.V));
+            if (gp.sh_k) GPS_LAUNCH(K_PROJECT, s, k_project_groups<true>, grid, dim3(kBlk), 0, s, dvt, rp, bs, gp, w);
+            else GPS_LAUNCH(K_PROJECT, s, k_project_groups<false>, grid, dim3(kBlk), 0, s, dvt, rp, bs, gp, w);
+        } else if (bs.per == kFewPer && bs.lds) launch_project<kFewWaves, kFewPer, true>(dvt, rp, bs, gp, w, s);
         else if (bs.per == kFewPer) launch_project<kFewWaves, kFewPer, false>(dvt, rp, bs, gp, w, s);
         else if (bs.lds) launch_project<kManyWaves, kManyPer, true>(dvt, rp, bs, gp, w, s);
         else launch_project<kManyWaves, kManyPer, false>(dvt, rp, bs, gp, w, s);
@@ -1206,7 +1370,7 @@ gps_status launch_render_fwd(const gps_render_cfg* cfg, const RParams& rp, const
         else GPS_LAUNCH(K_SCAN_TILES, s, k_scan_tiles<8>, dim3(1), dim3(1024), 0, s, rp, w, L.n_tiles);
     }
     if (bs.chunks > 0) {
-        if (bs.unsorted) launch_emit<1, kOrderGroup, false>(dvt, rp, bs, w, s);
+        if (bs.unsorted) GPS_LAUNCH(K_EMIT, s, k_emit_groups, dim3((unsigned int)(bs.chunks * rp.V)), dim3(kBlk), 0, s, dvt, rp, bs, w);
         else if (bs.per == kFewPer && bs.lds) launch_emit<kFewWaves, kFewPer, true>(dvt, rp, bs, w, s);
         else if (bs.per == kFewPer) launch_emit<kFewWaves, kFewPer, false>(dvt, rp, bs, w, s);
         else if (bs.lds) launch_emit<kManyWaves, kManyPer, true>(dvt, rp, bs, w, s);
