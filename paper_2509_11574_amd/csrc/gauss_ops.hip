@@ -361,32 +361,37 @@ __device__ __forceinline__ void write_gaussian(const InsertArgs& a, unsigned int
     if (a.out_pixel) a.out_pixel[pos] = p;
 }
 
-// Per new Gaussian (position pos < min(sampled, capacity)): kNN lanes search its nearest
+// Per new Gaussian (position pos < min(sampled, capacity)): NN lanes search its nearest
 // mask vertices together, then one lane of the block per Gaussian writes it.
 //
 // The search is a chain of dependent loads (a block's word, then the depths of its mask
-// pixels), so it is bound by latency: with one lane per Gaussian (72 blocks for the 18.4 k
-// Gaussians of a 1280x720 keyframe) it took 170 us, most of the chip idle.  Sixteen
+// pixels), so for a keyframe's few thousand it is bound by latency: with one lane per Gaussian (72
+// blocks for the 18.4 k Gaussians of a 1280x720 keyframe) it took 170 us, most of the chip idle.  Sixteen
 // lanes (a quarter of a wavefront, so that the group's exchanges stay in DPP rows) split each 8x8
 // block's 64 pixels four to a lane, read the words of up to 16 blocks of a ring in one round
 // trip, and keep a triple of smallest distances per lane that is merged once per ring; the
-// three smallest values are the same whatever the order of the search.
+// three smallest values are the same whatever the order of the search.  Where the whole image is
+// new, the groups' exchanges bound it, and eight lanes make fewer.  A 1280x720 frame's insertion with one, 16,
+// 8 and 4 lanes, in us: of 20 k 173, 60, 62, 78; of 36 k 118, 72, 70, 74; of 51 k 167, 84, 73, 84; of 203 k
+// 191, 233, 160, 143; of 903 k 638, 777, 521, 552.
 // The grid is bounded (the number of new Gaussians is only known on the device, and a capacity
 // of every pixel would launch 57,600 blocks at 1280x720, most of them empty); blocks stride.
-constexpr int kNN = 16;
+constexpr int kNNFew = 16, kNNMany = 8;
+constexpr unsigned int kFewNew = 32768;
 constexpr unsigned int kInitGrid = 2048;
 
-__global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
+// s_scale: one word per Gaussian of the block.
+template <int NN>
+__device__ __forceinline__ void insert_groups(const InsertArgs& a, unsigned int count, float* s_scale)
 {
     const int W = a.cam.W, H = a.cam.H;
-    constexpr int kPer = 256 / kNN;  // Gaussians per block
-    __shared__ float s_scale[kPer];
-    const unsigned int count = min(*a.total, (unsigned int)a.capacity);
+    constexpr int kPer = 256 / NN;    // Gaussians per block
+    constexpr int kBits = 64 / NN;   // pixels of an 8x8 block per lane
     const DevCam& c = a.cam;
     for (unsigned int pos0 = blockIdx.x * kPer; pos0 < count; pos0 += gridDim.x * kPer) {  // the same for the whole block
-        const unsigned int qpos = pos0 + threadIdx.x / kNN;
+        const unsigned int qpos = pos0 + threadIdx.x / NN;
         if (qpos < count) {
-            const int l = threadIdx.x % kNN;
+            const int l = threadIdx.x % NN;
             const int p = a.list[qpos];
             const int i = p % W, j = p / W;
             float X[3];
@@ -423,7 +428,7 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
                 const int bx0 = bi - r, bx1 = bi + r, by0 = bj - r, by1 = bj + r;
                 // The ring's blocks in the order top row, bottom row, left and right columns.
                 const int ring = r == 0 ? 1 : 8 * r, side = 2 * r + 1;
-                for (int q0 = 0; q0 < ring; q0 += kNN) {
+                for (int q0 = 0; q0 < ring; q0 += NN) {
                     // lane l looks at block q0 + l: in the image, and near enough to matter
                     const int q = q0 + l;
                     int bx, by;
@@ -437,21 +442,21 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
                     }
                     const unsigned long long mine = want ? a.bits[(size_t)by * a.nbx + bx] : 0ull;
                     // blocks of this batch that hold mask pixels, as bits of the group's lanes
-                    unsigned int have = (unsigned int)(__ballot(mine != 0ull) >> (threadIdx.x & 48)) & 0xffffu;
+                    unsigned int have = (unsigned int)(__ballot(mine != 0ull) >> (threadIdx.x & (64 - NN))) & ((1u << NN) - 1u);
                     const int at = bx | (by << 16);
                     while (have) {
                         const int src = __ffs((int)have) - 1;
                         have &= have - 1u;
-                        const unsigned int lo = __shfl((unsigned int)mine, src, kNN);
-                        const unsigned int hi = __shfl((unsigned int)(mine >> 32), src, kNN);
-                        const int xy = __shfl(at, src, kNN);
+                        const unsigned int lo = __shfl((unsigned int)mine, src, NN);
+                        const unsigned int hi = __shfl((unsigned int)(mine >> 32), src, NN);
+                        const int xy = __shfl(at, src, NN);
                         cnt += __popc(lo) + __popc(hi);
-                        // this lane's four pixels of the block: row l / 2, columns 4 (l & 1) .. + 3
-                        unsigned int nib = ((l < 8 ? lo : hi) >> (4 * (l & 7))) & 0xfu;
-                        const int jj = (xy >> 16) * 8 + (l >> 1), ii0 = (xy & 0xffff) * 8 + 4 * (l & 1);
-                        while (nib) {
-                            const int ii = ii0 + __ffs((int)nib) - 1;
-                            nib &= nib - 1u;
+                        // this lane's consecutive pixels of the block
+                        unsigned int part = ((l * kBits < 32 ? lo : hi) >> (l * kBits & 31)) & ((1u << kBits) - 1u);
+                        while (part) {
+                            const int k = l * kBits + __ffs((int)part) - 1;
+                            part &= part - 1u;
+                            const int ii = (xy & 0xffff) * 8 + (k & 7), jj = (xy >> 16) * 8 + (k >> 3);
                             if (ii == i && jj == j) continue;
                             float U[3];
                             cam_point(c, ii, jj, a.mdepth[(size_t)jj * W + ii], U);
@@ -476,8 +481,8 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
                 if (r == 0) --cnt;  // the query is a mask pixel of its own block
                 b0 = l0, b1 = l1, b2 = l2;
 #pragma unroll
-                for (int m = 1; m < kNN; m <<= 1) {
-                    const float c0 = __shfl_xor(b0, m, kNN), c1 = __shfl_xor(b1, m, kNN), c2 = __shfl_xor(b2, m, kNN);
+                for (int m = 1; m < NN; m <<= 1) {
+                    const float c0 = __shfl_xor(b0, m, NN), c1 = __shfl_xor(b1, m, NN), c2 = __shfl_xor(b2, m, NN);
                     merge3(b0, b1, b2, c0, c1, c2);
                 }
                 // distance bound of everything outside the scanned window
@@ -499,7 +504,7 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
                     const float sum = m == 1 ? b0 : (m == 2 ? b0 + b1 : (b0 + b1) + b2);
                     s1 = fminf(a.scale_cap, sqrtf(sum / (float)m));  // root mean square distance
                 }
-                s_scale[threadIdx.x / kNN] = s1;
+                s_scale[threadIdx.x / NN] = s1;
             }
         }
         __syncthreads();
@@ -507,6 +512,14 @@ __global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
         if (threadIdx.x < kPer && pos < count) write_gaussian(a, pos, s_scale[threadIdx.x]);
         __syncthreads();
     }
+}
+
+__global__ void __launch_bounds__(256) k_insert_init(InsertArgs a)
+{
+    __shared__ float s_scale[256 / kNNMany];
+    const unsigned int count = min(*a.total, (unsigned int)a.capacity);
+    if (count <= kFewNew) insert_groups<kNNFew>(a, count, s_scale);
+    else insert_groups<kNNMany>(a, count, s_scale);
 }
 
 size_t insertion_workspace_bytes(int W, int H)
@@ -561,7 +574,7 @@ gps_status launch_insert_gaussians(const gps_insert_cfg* cfg, const DevCam& cam,
     const size_t cap = (size_t)a.capacity < n ? (size_t)a.capacity : n;
     if (nblk > 0 && cap > 0) {
         GPS_LAUNCH(K_INSERT, s, k_insert_place, dim3(nblk), dim3(256), 0, s, a);
-        GPS_LAUNCH(K_INSERT, s, k_insert_init, dim3(std::min((unsigned)((cap + 256 / kNN - 1) / (256 / kNN)), kInitGrid)), dim3(256), 0, s, a);
+        GPS_LAUNCH(K_INSERT, s, k_insert_init, dim3(std::min((unsigned)((cap + 256 / kNNFew - 1) / (256 / kNNFew)), kInitGrid)), dim3(256), 0, s, a);
     }
     return hipGetLastError() == hipSuccess ? GPS_OK : GPS_ERR_HIP;
 }
