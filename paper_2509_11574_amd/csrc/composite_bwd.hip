@@ -6,9 +6,8 @@
 // transpose-reduction within each 16-lane row, LDS across rows and wavefronts,
 // fixed order) and writes one 10-float partial per (tile, Gaussian) instance
 // into that instance's slot: the view-Gaussian's first slot plus the tile's
-// place in its tile rectangle.  Instances after the point where every pixel of
-// the tile has stopped keep the zeros the emission wrote.  No floating-point
-// atomics.
+// place in its tile rectangle.  The slots of instances after the point where every
+// pixel of the tile has stopped are zeroed at the end.  No floating-point atomics.
 #include "launch.h"
 #include "prof.h"
 #include "render_common.h"

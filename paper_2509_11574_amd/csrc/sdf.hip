@@ -330,10 +330,13 @@ __global__ void __launch_bounds__(256) k_raycast(MarchArgs a, DenseField<NARROW>
 {
     const int view = blockIdx.z;
     const DevCam& c = a.cams[view];
-    // 16x16 pixels a block, 8x8 a wavefront
+    // 16x16 pixels a block, 8x8 a wavefront; 16x4 where every sample is evaluated, which then reads fewer lines a
+    // stencil (without brick minima, 8x8 and 16x4 in us: 640x480 view of 400^3 points 466 and 459, of 512^3 605
+    // and 587; with them 88 and 92, 100 and 100, a 1280x720 view of 512^3 126 and 133)
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int col = blockIdx.x * 16 + (wid & 1) * 8 + (lane & 7);
-    const int row = blockIdx.y * 16 + (wid >> 1) * 8 + (lane >> 3);
+    const int dx = fld.bmin ? (wid & 1) * 8 + (lane & 7) : lane & 15;
+    const int dy = fld.bmin ? (wid >> 1) * 8 + (lane >> 3) : wid * 4 + (lane >> 4);
+    const int col = blockIdx.x * 16 + dx, row = blockIdx.y * 16 + dy;
     if (col >= c.W || row >= c.H) return;
     const DenseField<NARROW> f = fld;  // this lane's copy (it keeps the last brick found not positive)
     march_pixel(a, f, view, col, row);

@@ -269,10 +269,11 @@ __device__ __forceinline__ void march_pixel(const MarchArgs& a, const Fld& fld, 
         far[k] = gd >= 0.0f ? 1.0f : 0.0f;
     }
     // Steps kept back before a box's exit.  A sample that overshoots the box by a fraction e of a
-    // step lies at most e / 2 voxels beyond points that are all above kBrickPositive and reads at
-    // least kBrickPositive - e, so what has to be covered is the rounding of the exit and of the
-    // sample's own position, a few 2^-24 of the coordinates; a whole step costs each box
-    // a second visit for one sample.
+    // step of h voxels lies at most e h voxels beyond, along any axis, points that are all above
+    // kBrickPositive, and reads at least kBrickPositive - 3 e h; so what has to be covered is the
+    // rounding of the exit and of the sample's own position, a few 2^-24 of the coordinates.  (An
+    // axis along which the ray hardly moves rounds its exit by more steps, but by no more voxels.)
+    // A whole step costs each box a second visit for one sample.
     const float slack =
         fminf(1.0f, 0.01f + 1e-6f * a.inv_h *
                                 (fmaxf(fmaxf(fabsf(o[0]), fabsf(o[1])), fabsf(o[2])) +
