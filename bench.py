@@ -132,6 +132,16 @@ def parse():
     return ap.parse_args()
 
 
+def centres_in_view(mean, cam, z_near) -> int:
+    """Gaussians whose centre projects into the image in front of z_near."""
+    import torch
+
+    R = torch.as_tensor(cam["R"], dtype=torch.float32, device=mean.device).reshape(3, 3)
+    x, y, z = R @ mean + torch.as_tensor(cam["t"], dtype=torch.float32, device=mean.device).reshape(3, 1)
+    u, v = cam["fx"] * x / z + cam["cx"], cam["fy"] * y / z + cam["cy"]
+    return int(((z > z_near) & (u > -0.5) & (u < cam["width"] - 0.5) & (v > -0.5) & (v < cam["height"] - 0.5)).sum())
+
+
 def _kname(name: str) -> str:
     """A rocprofv3 kernel name without its return type and argument list."""
     name = name.split("(")[0].strip()
@@ -478,6 +488,9 @@ def main():
         launches, total = kernels[dom]
         avg_s = total / launches / 1000.0
         if dom in ("composite_fwd", "composite_bwd"):
+            # The evaluated pairs are the forward's; where the backward runs with more pixels a lane (small
+            # grids, composite_cfgs) it evaluates more, and its flops are a lower bound.
+            shapes = P.gps.composite_cfgs(cfg, M, [cams[Wu].as_dict()])
             per = FLOPS_CONTRIB_FWD if dom == "composite_fwd" else FLOPS_CONTRIB_BWD
             flops = FLOPS_EVAL * pairs["eval_per_launch"] + per * pairs["contrib_per_launch"]
             ach = flops / avg_s / 1e12
@@ -486,7 +499,10 @@ def main():
             roofline = {"bound": "alu", "kernel": dom, "achieved": round(ach, 3), "peak": FP32_PEAK_TFLOPS,
                         "unit": "TFLOP/s", "frac": round(ach / FP32_PEAK_TFLOPS, 4),
                         "traffic": tr[0], "traffic_by_request_size": tr[1],
-                        "avg_launch_ms": round(avg_s * 1e3, 4), "flops_per_launch": flops}
+                        "avg_launch_ms": round(avg_s * 1e3, 4), "flops_per_launch": flops,
+                        "pixels_per_lane": {"fwd": shapes[0].pix_per_thread, "bwd": shapes[1].pix_per_thread},
+                        "flops_are": "exact" if shapes[0].pix_per_thread == shapes[1].pix_per_thread
+                        or dom == "composite_fwd" else "a lower bound"}
         else:
             roofline = {"bound": "hbm", "kernel": dom, "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": None, "traffic": None, "avg_launch_ms": round(avg_s * 1e3, 4)}
@@ -494,8 +510,11 @@ def main():
     # ------------------------------ whole-iteration algorithmic HBM bytes
     I = st1["n_instances"]
     Pp = W_img * H_img
-    bytes_iter = (56 * M + 48 * M + 8 * M            # project: params in, records + counts out
-                  + 12 * I + 8 * M + 16 * I          # emit (keys, slots), tile sort (read + write)
+    # S: Gaussians with a record; counted by their centres, so those that reach in from outside are missing.
+    # I counts tile slots, of which about a tenth is culled and gets no key.
+    S = centres_in_view(params["mean"], cams[Wu + K].as_dict(), cfg.z_near)
+    bytes_iter = (56 * M + 4 * M + 60 * S            # project: params in, slot counts out, records + walk of those seen
+                  + 4 * M + 16 * S + 8 * I + 16 * I  # emit: walk in, first slots and keys out; tile sort (read + write)
                   + 60 * I + 48 * Pp                 # composite fwd: keys/slots/records, base+target+out
                   + 60 * I + 40 * I + 64 * Pp        # composite bwd: instances, partials out, per-pixel in
                   + 40 * I + 56 * M + 8 * M          # per-Gaussian reduce: partials, params in, slot offsets

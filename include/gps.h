@@ -310,7 +310,7 @@ gps_status gps_hash_reset(const gps_hash_volume* vol, void* stream);
  * gps_fuse on a dense lattice whose points outside the allocated blocks are left
  * alone.  A full pool or table sets a status bit in state[3] (sticky until
  * gps_hash_reset); blocks without room are then read as unallocated.
- * depth [H][W], rgb [3][H][W].  Five kernels, nothing read back. */
+ * depth [H][W], rgb [3][H][W].  Four kernels, nothing read back. */
 gps_status gps_hash_fuse(const gps_hash_volume* vol, const gps_camera* cam, const float* depth, const float* rgb,
                          void* stream);
 

@@ -26,6 +26,9 @@ constexpr int kKeptBits = 32;         // slots of a Gaussian whose culls are kep
 //                   87 and 35.
 //   many:           4 of 64, which fill the chip: 8 wavefronts a SIMD.  (16 of 64, for fewer
 //                   rows, measured the same.)
+// Few / many at 40 k, 131 k, 170 k and 380 k (project, scans, emit in us): a 1280x720 view in tiles of 16x32
+// 36 / 37, 38 / 39, 46 / 45 and 65 / 61; a 640x480 view in tiles of 8x8 46 / 51, 59 / 62, 68 / 71 and
+// 88 / 89; four 640x480 views in tiles of 16x16 36 / 40, 46 / 42, 50 / 50 and 62 / 61.
 constexpr int kFewWaves = 8, kFewPer = 32, kManyWaves = 4, kManyPer = 64;
 constexpr long long kFewGaussians = 131072;  // over the views
 constexpr int kMostWaves = 8192;             // over the views
