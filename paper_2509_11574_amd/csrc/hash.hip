@@ -486,9 +486,10 @@ __global__ void __launch_bounds__(256) k_hash_range(HashDev h, MarchArgs a, Hash
 // 226 us for that view; what remains is the directory's arithmetic in front of each stencil.
 // A region of kDirBlocks blocks takes 72 KB, so that two workgroups of 16 wavefronts fill a
 // compute unit; that, and pool blocks below 0xffff, is where the line to the table lookups lies.  One
-// workgroup a compute unit would still be the faster route beyond: the raycast of a 1280x720 view takes 175 us
-// at 256^3; at 264^3, 288^3 and 320^3 it takes 421, 464 and 483 us with table lookups and the depth ranges, and
-// measured with a directory of up to 65535 blocks 262, 281 and 274.  The line has been left at two.
+// workgroup a compute unit would still be the faster route beyond: the raycast of a 1280x720 view of
+// another room takes 175 us at 256^3; at 264^3, 288^3 and 320^3 it takes 421, 464 and 483 us with table
+// lookups and the depth ranges, and took 262, 281 and 274 with a directory of up to 65535 blocks.  The line
+// has been left at two.
 constexpr int kDirBlocks = 32768;
 constexpr int kDirWords = 1536;  // words of one bit plane
 constexpr unsigned int kDirNone = 0xffffu;
